@@ -107,7 +107,9 @@ def launch_work(info, work, split):
     parts (its batch index in `split`): a child-sum batch on the large tile,
     part 2 the per-child forget GEMM, part 1 the per-parent sums (no flops),
     part 0 the parents' main GEMM; an MV-RNN vector batch, part 1 the
-    matrix-vector products, part 0 its GEMM."""
+    matrix-vector products, part 0 its GEMM; a team launch, all its batches."""
+    if info.get("variant") == TEAM_VARIANT:
+        return sum(work[b][0] + work[b][1] for b in range(info["batch"], info["batch"] + info["n_batches"]))
     fl, flr, _ = work[info["batch"]]
     part = info["part"]
     if part == 2:
@@ -120,6 +122,7 @@ def launch_work(info, work, split):
 # small-tile variants (rows 16*RT, units 16*WU, split-K WK), in the library's order
 SMALL_VARIANTS = [(2, 4, 1), (1, 4, 1), (1, 2, 2), (1, 1, 4), (1, 1, 8), (1, 1, 16), (2, 1, 4), (2, 2, 2)]
 STREAM_SHAPES = {11: (1, 4), 12: (2, 4), 13: (1, 8), 14: (1, 16)}   # streamed tile: (rows / 16, waves)
+TEAM_VARIANT = 101                                                  # team launch: the tail of the schedule in one launch
 LARGE_CLASS = {8: 0, 9: 1, 10: 2, 15: 3, 16: 4}                     # large tile: size class
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
@@ -132,6 +135,8 @@ KIND_NAMES = {0: "LSTM_CHAIN", 1: "NARY_LEAF", 2: "NARY_INTERNAL", 3: "GRID", 4:
 def kernel_name(kind, variant, part, dtype):
     """A readable name of the kernel a launch runs (kind, tile family, variant)."""
     from paper_2302_03851_amd import _lib as L
+    if variant == TEAM_VARIANT:
+        return f"team_kernel<{dtype}>"
     kname = KIND_NAMES[kind]
     if part == 1:
         return "mv_matvec_kernel" if kind == 12 else "child_reduce_kernel"
@@ -150,6 +155,8 @@ def kernel_symbol(kind, dtype, variant, part):
     if part == 1:
         return "edbk::mv_matvec_kernel" if kind == 12 else "edbk::child_reduce_kernel"
     t = 'float' if dtype == 'f32' else '__bf16'
+    if variant == TEAM_VARIANT:
+        return f"edbk::team_kernel<{t},"
     from paper_2302_03851_amd import _lib as L
     if variant == L.WS_VARIANT:
         return f"edbk::ws_kernel<{kind}>"
@@ -862,7 +869,7 @@ def main():
         if dom == (WL.MV_VEC, -1, 1):
             by_launch = sum(inf["m"] for inf in grp) * (2 * w.hidden + 2) * w.hidden * esz_d / nl
         else:
-            by_launch = sum(work[inf["batch"]][2] for inf in grp) / nl
+            by_launch = sum(work[b][2] for inf in grp for b in range(inf["batch"], inf["batch"] + inf["n_batches"])) / nl
         gbs = by_launch / (avg_ms * 1e-3) / 1e9
     kind_v, var_v, part_v = dom
     kernel = kernel_name(kind_v, var_v, part_v, w.dtype)

@@ -344,10 +344,12 @@ edb_status edb_pack_weights(const edb_cell* cell, const float* const* logical,
 #define EDB_FORCE_GATHER 4  /* treat every CONTIG operand as indexed (ablation) */
 #define EDB_X_DIRECT     8  /* read x rows in place by x_row instead of staging them */
 #define EDB_PROFILE     16  /* eager launches timed by start/stop HIP events in each dispatch (edb_exec_launch_times) */
-#define EDB_NO_FLOW     32  /* one launch per batch only (no dataflow launches) */
+#define EDB_NO_FLOW     32  /* one launch per batch only (no dataflow launches, no team launch) */
 #define EDB_NO_SPLIT_K  64  /* small tiles without split-K only (each accumulator sums its k-groups in order) */
 #define EDB_TILE_LARGE 128  /* the large bf16 tile for every batch it supports, whatever the batch size */
 #define EDB_NO_LARGE   256  /* never the large tile (ablation) */
+#define EDB_TEAM_DRYRUN 1024 /* with EDB_DRYRUN only: build the team launch as for a device of 256
+                               compute units, so that edb_exec_validate can check its descriptors */
 #define EDB_FLOW_DRYRUN 512 /* with EDB_DRYRUN only: build the dataflow launches (switched off on the
                                GPU) so that edb_exec_validate can check their descriptors */
 
@@ -395,8 +397,8 @@ edb_status edb_prepare(const edb_graph_t* g, const edb_schedule_t* s, const edb_
  * The call zeroes the arena's zero row and pad rows, stages x, then runs
  * every batch in schedule order.  x is not staged under EDB_X_DIRECT, when
  * every node's staged row would be its own row of x (x is then read in
- * place), or when a single batch reads x (it then reads the caller's rows
- * through its row list, as under EDB_X_DIRECT).  With
+ * place), or when a single batch, or only batches of the team launch, read x
+ * (they then read the caller's rows by their numbers, as under EDB_X_DIRECT).  With
  * EDB_USE_GRAPH the sequence runs as one launch of a HIP graph that the
  * library keeps per device and stream and reuses for every later execution
  * there, of any executor, whose sequence has the same kernels and block sizes
@@ -416,7 +418,23 @@ edb_status edb_execute(edb_exec_t* e, const void* const* packed_weights, const v
  * cost a new instantiation).  Host outputs; EDB_ERR_INVALID on NULL. */
 edb_status edb_graph_stats(int64_t* instantiated, int64_t* updated);
 
-/* Dataflow launches (a persistent kernel running a run of consecutive small
+/* Team launch: where it is estimated to be faster, the last batches of the
+ * schedule (all of them for a chain or a lattice) run as one launch.  The
+ * connected components of those batches (the instances, or parts of them) are
+ * dealt to teams of ceil(H / 16) work-groups (ceil(H / 32) for bf16 above 256
+ * units), at most 32; each work-group keeps its units' weights in registers
+ * and walks the team's rows batch by batch, the work-groups of a team
+ * exchanging h rows through the arena.  It serves tails of one cell type among
+ * LSTM_CHAIN, NARY_INTERNAL, GRU_INTERNAL, GRID and CS_INTERNAL (at most 32
+ * children a node), two NARY_INTERNAL types, LAT_CHAR (at most 16 words a
+ * node) with LAT_WORD, and LGRU_EDGE with POOL_MEAN, within the sizes that fit
+ * the registers and the LDS; not under EDB_NO_FLOW, EDB_NO_SPLIT_K,
+ * EDB_TILE_LARGE, EDB_NO_LARGE or a forced variant.  A row's states do not
+ * depend on how rows were dealt.  Waits between work-groups are bounded (over
+ * a second; the environment variable EDB_SPIN_US shortens them for tests):
+ * edb_exec_check reports one that timed out.
+ *
+ * Dataflow launches (a persistent kernel running a run of consecutive small
  * batches, each tile waiting only for the tiles that produce its operand
  * rows) are currently switched off: every batch runs as its own launch and
  * EDB_NO_FLOW has no effect.  edb_exec_check reports a timed-out dataflow
@@ -425,21 +443,23 @@ edb_status edb_graph_stats(int64_t* instantiated, int64_t* updated);
  * Number of launch records of one edb_execute: record 0 is the staging launch
  * (x staging and the clearing of the zero and pad rows), then the batches'
  * launches.  Record 0 has grid 0 and is not issued when nothing is staged and
- * the first batch (no child lists, no x padding) clears those rows itself. */
+ * the first batch (no child lists, no x padding) clears those rows itself.
+ * The launch that clears them also marks a team launch's rows as not written. */
 edb_status edb_exec_launches(const edb_exec_t* e, int32_t* n_kernels);
 
 /* Description of launch i (for tests and profiling). */
 typedef struct {
-    int32_t batch;     /* batch index (first batch of a dataflow launch), -1 for the staging kernel */
-    int32_t kind;      /* EDB_CELL_* of the batch, -1 for staging and dataflow launches */
-    int32_t m;         /* rows (all batches of a dataflow launch) */
+    int32_t batch;     /* batch index (first batch of a dataflow or team launch), -1 for the staging kernel */
+    int32_t kind;      /* EDB_CELL_* of the batch, -1 for staging, dataflow and team launches */
+    int32_t m;         /* rows (all batches of a dataflow or team launch) */
     int32_t k;         /* padded reduction length of the main GEMM */
     int32_t n;         /* padded output columns (gates x padded hidden) */
     int32_t variant;   /* tile variant id: 0-7 small tiles, 8-10 and 15-16 the large tile (size
                           classes 0-4: 256, 128, 64 rows x 64 units, then 64 and 32 rows x 32
                           units, fewer rows for 5-gate cells), 11-14 streamed tiles (counterparts
                           of the small tiles 3, 6, 4, 5), 17 the weight-stationary tile
-                          (256-row tiles x 32 units, 512 threads), 100 a dataflow launch */
+                          (256-row tiles x 32 units, 512 threads), 100 a dataflow launch,
+                          101 a team launch */
     int32_t grid;      /* work-groups */
     int32_t block;     /* threads per work-group */
     int32_t seg_kind[4]; /* kinds of result, child 0, child 1, ragged lists */
@@ -544,7 +564,7 @@ edb_status edb_forward_noalloc(int32_t n_nodes, int32_t n_types, const int32_t* 
  * EDB_ERR_INVALID with the first problem found in edb_last_error(). */
 edb_status edb_exec_validate(const edb_exec_t* e, int32_t n_workers, int64_t* checked);
 
-/* Wait for `stream` and check the last execution's dataflow launches:
+/* Wait for `stream` and check the last execution's dataflow and team launches:
  * EDB_ERR_HIP if a bounded wait timed out (the results are then invalid). */
 edb_status edb_exec_check(edb_exec_t* e, void* stream);
 
@@ -568,6 +588,7 @@ edb_status edb_exec_check(edb_exec_t* e, void* stream);
  * ms (may be NULL): host float[n], n >= 2 * n_batches; receives per batch the
  * gather and the scatter kernel's duration in milliseconds (HIP events in the
  * dispatch packets); the call then waits for the stream.
+ * Batches inside a team launch are copied like the others.
  * Errors: EDB_ERR_INVALID, EDB_ERR_UNSUPPORTED (a batch inside a dataflow
  * launch), EDB_ERR_HIP. */
 edb_status edb_split_phase_bytes(const edb_exec_t* e, int64_t* bytes);

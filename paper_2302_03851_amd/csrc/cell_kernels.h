@@ -83,6 +83,12 @@ struct BatchArgs {
     float* fc;            // child-sum batches on the large tile: sigma(f_k) * c_k per child, [children][H]
     const int* zrows;     // rows this launch clears in both arenas (the zero row and pads), or none
     int n_zero;
+    // then (with n_zero > 0) the rows of a later team launch: n_fill_h rows of h and n_fill_c
+    // rows of c at frows that start out empty, and its counters
+    const int* frows;
+    int n_fill_h, n_fill_c;
+    int* ints;
+    int nint;
 };
 
 
@@ -178,6 +184,19 @@ __device__ __forceinline__ void clear_zero_rows(const BatchArgs& a) {
         h[o] = from_f<T>(0.f);
         a.arena_c[o] = 0.f;
     }
+    // rows that a team launch waits for: every bit set, in whole 16-byte pieces
+    const int vh = a.H * (int)sizeof(T) / 16, vc = a.H / 4;
+    const int64_t nh = (int64_t)a.n_fill_h * vh, nc = (int64_t)a.n_fill_c * vc;
+    const uint4 ones = make_uint4(~0u, ~0u, ~0u, ~0u);
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nh + nc; i += (int64_t)gridDim.x * blockDim.x) {
+        if (i < nh) reinterpret_cast<uint4*>(a.arena_h)[(int64_t)a.frows[i / vh] * vh + i % vh] = ones;
+        else {
+            const int64_t k = i - nh;
+            reinterpret_cast<uint4*>(a.arena_c)[(int64_t)a.frows[a.n_fill_h + k / vc] * vc + k % vc] = ones;
+        }
+    }
+    if (blockIdx.x == 0)
+        for (int i = threadIdx.x; i < a.nint; i += blockDim.x) a.ints[i] = 0;
 }
 
 // Gate nonlinearities and cell-state update of one (node, unit) element.
@@ -1433,13 +1452,16 @@ __global__ __launch_bounds__(256) void flow_kernel(FlowArgs f) {
 // 4 rows with one wave per row.
 //   rows [0, n_x): xs[i] = x[src[i]]          (row length E elements of T)
 //   rows [n_x, n_x + n_zero): arena row zrow[i] of h and c set to zero
-//   work-group 0 also clears the `nint` dataflow counters at `ints`
+//   then n_fill_h rows of h and n_fill_c rows of c (listed at frow) set to the
+//   empty pattern of a team launch (every bit set)
+//   work-group 0 also clears the `nint` counters at `ints`
 template <typename T>
 __global__ __launch_bounds__(256) void stage_kernel(const T* __restrict__ x, T* __restrict__ xs,
                                                     const int* __restrict__ src, int n_x, int E,
                                                     const int* __restrict__ zrow, int n_zero,
                                                     T* __restrict__ arena_h, float* __restrict__ arena_c,
-                                                    int H, int* __restrict__ ints, int nint) {
+                                                    int H, int* __restrict__ ints, int nint,
+                                                    const int* __restrict__ frow, int n_fill_h, int n_fill_c) {
     constexpr int V = Elem<T>::VEC;
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < nint; i += blockDim.x) ints[i] = 0;
@@ -1455,6 +1477,13 @@ __global__ __launch_bounds__(256) void stage_kernel(const T* __restrict__ x, T* 
         for (int c = lane; c < H / V; c += 64) dh[c] = make_uint4(0, 0, 0, 0);
         float4* dc = reinterpret_cast<float4*>(arena_c + (size_t)z * H);
         for (int c = lane; c < H / 4; c += 64) dc[c] = make_float4(0.f, 0.f, 0.f, 0.f);
+    } else if (row < n_x + n_zero + n_fill_h + n_fill_c) {
+        const int i = row - n_x - n_zero;
+        const bool is_h = i < n_fill_h;
+        uint4* d = is_h ? reinterpret_cast<uint4*>(arena_h + (size_t)frow[i] * H)
+                        : reinterpret_cast<uint4*>(arena_c + (size_t)frow[i] * H);
+        const int nv = is_h ? H / V : H / 4;
+        for (int c = lane; c < nv; c += 64) d[c] = make_uint4(~0u, ~0u, ~0u, ~0u);
     }
 }
 

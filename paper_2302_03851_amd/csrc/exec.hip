@@ -23,6 +23,8 @@
 #include "diag_kernels.h"
 #include "mv_kernels.h"
 #include "edb_internal.h"
+#include "team.h"
+#include "team_kernel.h"
 
 using edb::fail;
 using namespace edbk;
@@ -405,9 +407,16 @@ struct Launch {
     bool flow = false;
     int64_t f_desc, f_tiles, f_rtdeps, f_deps, f_ticket, f_error, f_done;
     int f_ntiles, f_need;
+    // team launch (info.variant == TEAM_VARIANT)
+    bool team = false;
+    const void* team_fn = nullptr;
+    int team_type[2] = {-1, -1};
+    int team_P = 0, team_C = 0, team_ub = 1, team_blk = 0, team_limit = 0, team_rows = 0;
+    int64_t off_team = -1, off_ticket = -1;   // table of the teams' blocks; {ticket, error}
 };
 
 constexpr int FLOW_VARIANT = 100;
+constexpr int TEAM_VARIANT = 101;
 
 template <typename T>
 int flow_lds(const std::vector<int>& kinds_k) {
@@ -545,6 +554,40 @@ int best_large(int kk, int dtype, int G, int m, int K, int Hu, int n_cu, int max
 
 }  // namespace
 
+// Team launches in flight per device.  A team launch whose work-groups are not
+// all running holds the CUs of a last, incomplete team until its other members
+// find room: at most P - 1 work-groups, dealt round-robin to the 8 XCDs, so at
+// most 2 of an XCD's 32 CUs for teams of up to 16 work-groups and 4 for teams of
+// 32.  With enough launches in flight these could fill an XCD on which every one
+// of them waits for room (seen at 16 streams).  So a launch first waits for the
+// one kTeamsInFlight launches earlier, unless that ran on its own stream: 4
+// launches hold at most 16 CUs of an XCD, which leaves room for more of them
+// from other processes.
+constexpr int kTeamsInFlight = 4;
+struct TeamGate {
+    std::mutex mu;
+    hipEvent_t done[kTeamsInFlight] = {};     // after the launch; kept for the process
+    hipStream_t stream[kTeamsInFlight] = {};
+    int next = 0;
+
+    // with mu held, before and after the launch on st
+    hipError_t enter(hipStream_t st) {
+        if (!done[next]) return hipEventCreateWithFlags(&done[next], hipEventDisableTiming);
+        if (stream[next] == st) return hipSuccess;
+        const hipError_t q = hipEventQuery(done[next]);
+        if (q != hipErrorNotReady) return q;
+        (void)hipGetLastError();
+        return hipStreamWaitEvent(st, done[next], 0);
+    }
+    hipError_t leave(hipStream_t st, hipEvent_t* last) {
+        const hipError_t he = hipEventRecord(done[next], st);
+        *last = done[next];
+        stream[next] = st;
+        next = (next + 1) % kTeamsInFlight;
+        return he;
+    }
+};
+
 // Per-device state shared by all executors: the LDS limit, a non-blocking
 // upload stream for descriptor copies (kept for the life of the process) and
 // the largest dynamic LDS size already granted to each kernel.
@@ -555,8 +598,10 @@ struct DeviceCtx {
     hipStream_t release = nullptr;   // stream-ordered frees wait here, off the upload path
     void* scratch = nullptr;         // this device's address of the allocation-free entry point's array
     std::map<int, int> lds_granted;
+    std::map<const void*, int> team_lds;     // likewise of each team kernel
     std::map<std::pair<const void*, int>, int> occupancy;   // (kernel, dynamic LDS) -> resident work-groups per CU
     std::vector<hipEvent_t> event_pool;      // timing events of freed EDB_PROFILE executors, for reuse
+    std::shared_ptr<TeamGate> teams = std::make_shared<TeamGate>();
 };
 std::mutex g_ctx_mu;
 std::map<int, DeviceCtx> g_ctx;
@@ -610,7 +655,10 @@ struct edb_exec {
     std::vector<Launch> launches;     // [0] = staging, then one per batch
     int32_t n_zero = 0;
     int64_t off_xsrc = 0, off_zero = 0;
-    int64_t off_counters = 0, n_counters = 0;   // dataflow counters, cleared every forward
+    int64_t off_counters = 0, n_counters = 0;   // counters of dataflow and team launches, cleared every forward
+    int64_t off_fill = 0;                        // rows of a team launch that start out empty
+    int32_t n_fill_h = 0, n_fill_c = 0;
+    std::vector<Launch> team_batches;            // the operand lists of the batches inside the team launch
     std::vector<int32_t> hbuf;        // host copy of the device int buffer
     void* dmem = nullptr;             // one stream-ordered allocation: dbuf | xstaged | scratch rows
     bool dmem_async = true;           // allocated with hipMallocAsync
@@ -630,6 +678,9 @@ struct edb_exec {
     int device = -1;
 
     DeviceCtx* ctx = nullptr;
+    std::shared_ptr<TeamGate> teams;
+    hipEvent_t team_done = nullptr;   // the gate's event of the last execution, where it ended with a team launch
+    bool uploaded = false;            // the descriptors are known to be on the device
 
     ~edb_exec() {
         // timing events go back to the device's pool (creating them costs
@@ -642,12 +693,15 @@ struct edb_exec {
             for (hipEvent_t ev : events) (void)hipEventDestroy(ev);
         }
         if (dmem && dmem_owned) {
+            // (a team launch's place in the gate may hold a later launch by now: that
+            // one waited for this executor's)
+            const hipEvent_t last = team_done ? team_done : done;
             // free in stream order after the upload and the last execution, on a
             // stream of its own so that later uploads do not queue behind this
             // executor's kernels
             if (dmem_async) {
                 (void)hipStreamWaitEvent(release, ready, 0);
-                if (ran && done) (void)hipStreamWaitEvent(release, done, 0);
+                if (ran && last) (void)hipStreamWaitEvent(release, last, 0);
                 (void)hipFreeAsync(dmem, release);
             } else {
                 (void)hipFree(dmem);
@@ -712,8 +766,10 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
     *out = nullptr;
     if (!g || !s || !p || !cells) return fail(EDB_ERR_INVALID, "edb_prepare: NULL argument");
     if (flags & ~(EDB_USE_GRAPH | EDB_DRYRUN | EDB_FORCE_GATHER | EDB_X_DIRECT | EDB_PROFILE | EDB_NO_FLOW |
-                  EDB_NO_SPLIT_K | EDB_TILE_LARGE | EDB_NO_LARGE | EDB_FLOW_DRYRUN))
+                  EDB_NO_SPLIT_K | EDB_TILE_LARGE | EDB_NO_LARGE | EDB_FLOW_DRYRUN | EDB_TEAM_DRYRUN))
         return fail(EDB_ERR_INVALID, "edb_prepare: unknown flags");
+    if ((flags & EDB_TEAM_DRYRUN) && !(flags & EDB_DRYRUN))
+        return fail(EDB_ERR_INVALID, "edb_prepare: EDB_TEAM_DRYRUN needs EDB_DRYRUN");
     if ((flags & EDB_FLOW_DRYRUN) && !(flags & EDB_DRYRUN))
         return fail(EDB_ERR_INVALID, "edb_prepare: EDB_FLOW_DRYRUN needs EDB_DRYRUN (dataflow launches are switched off)");
     if ((flags & EDB_TILE_LARGE) && (flags & EDB_NO_LARGE))
@@ -808,6 +864,7 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             e->device = dev;
             max_lds = ctx->max_lds;
             n_cu = ctx->n_cu;
+            e->teams = ctx->teams;
         }
         const int force_var = std::getenv("EDB_VARIANT") ? std::atoi(std::getenv("EDB_VARIANT")) : -1;
         // occupancy per (kernel, dynamic LDS): the device context's cache is
@@ -845,7 +902,6 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             L.info.batch = -1;
             L.info.kind = -1;
             L.info.m = n_x;
-            L.info.grid = (((flags & EDB_X_DIRECT) || e->x_in_place ? 0 : n_x) + e->n_zero + 3) / 4;   // 4 rows per work-group
             L.info.block = 256;
             L.info.variant = -1;
             L.info.n_batches = 0;
@@ -853,8 +909,11 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
         }
         const bool force_gather = (flags & EDB_FORCE_GATHER) != 0;
         std::vector<std::vector<Launch>> blaunch;   // the launches of each batch, in order
-        blaunch.reserve(B);
-        for (int32_t b = 0; b < B; ++b) {
+        std::vector<double> bcost;                  // their estimated microseconds
+        blaunch.resize(B);
+        bcost.assign(B, 0.0);
+        // batch b's operand lists, without a kernel yet
+        auto lists = [&](int32_t b) {
             const int32_t t = s->batch_type[b];
             const Dims& d = dims[t];
             const int32_t m = s->batch_ptr[b + 1] - s->batch_ptr[b];
@@ -911,6 +970,14 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
                     a.x = Seg{S_CONTIG, xb, nullptr};
                 }
             }
+            return L;
+        };
+        // batch b's launches: its tile variant and their estimated time
+        auto choose = [&](int32_t b) -> edb_status {
+            const int32_t t = s->batch_type[b];
+            const Dims& d = dims[t];
+            const int32_t m = s->batch_ptr[b + 1] - s->batch_ptr[b];
+            Launch L = lists(b);
             // tile variant: smallest estimated time under a simple model (matrix
             // core cycles of the busiest SIMD plus per-k-group latency), ties
             // to the larger tile; variants whose LDS need exceeds the device
@@ -980,7 +1047,6 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
                 if (ws_ok && ((m >= kWsMinRows && force_var < 0) || force_var == WS_VARIANT)) var = WS_VARIANT;
             }
             if (var < 0) {
-                delete e;
                 return fail(EDB_ERR_UNSUPPORTED, "edb_prepare: no tile variant fits the LDS of batch " +
                                                      std::to_string(b));
             }
@@ -991,7 +1057,6 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
                 const int64_t ro = p->ragged_off[b];
                 for (int32_t r = 0; r < m; ++r)
                     if (p->ragged_pool[ro + r + 1] - p->ragged_pool[ro + r] != 2 * d.H) {
-                        delete e;
                         return fail(EDB_ERR_INVALID, "edb_prepare: an MV_VEC node of batch " + std::to_string(b) +
                                                          " does not list exactly 2 * hidden matrix columns");
                     }
@@ -1057,7 +1122,6 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             }
             L.lds = table().e[L.kk][dtype][var].lds(d.K, d.Hk);
             if (L.lds > max_lds) {
-                delete e;
                 return fail(EDB_ERR_UNSUPPORTED, "edb_prepare: LDS need of batch " + std::to_string(b) +
                                                      " exceeds the device limit");
             }
@@ -1090,7 +1154,25 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
                 L.info.block = 64 * VAR_WU[var] * VAR_WK[var];
             }
             parts.push_back(L);
-            blaunch.push_back(std::move(parts));
+            blaunch[b] = std::move(parts);
+            bcost[b] = std::min(best, lest);
+            return EDB_OK;
+        };
+        // A batch of few rows that a team launch may take (below) is not given
+        // launches of its own before that is decided; its cost is about its
+        // kernel's floor (4.1 us, 3.5 more with ragged children, and its weights).
+        const bool team_ok = force_var < 0 && large_fits &&
+                             !(flags & (EDB_NO_FLOW | EDB_NO_SPLIT_K | EDB_TILE_LARGE | EDB_NO_LARGE | EDB_FLOW_DRYRUN)) &&
+                             (!(flags & EDB_DRYRUN) || (flags & EDB_TEAM_DRYRUN));
+        const int few = team_ok ? 4 * std::max(1, n_cu / std::max(1, (H + 15) / 16)) : 0;
+        for (int32_t b = 0; b < B; ++b) {
+            const Dims& d = dims[s->batch_type[b]];
+            if (s->batch_ptr[b + 1] - s->batch_ptr[b] <= few) {
+                bcost[b] = 4.1 + (d.rag ? 3.5 : 0.0) + 0.003 * d.K;
+            } else if (edb_status st = choose(b)) {
+                delete e;
+                return st;
+            }
         }
 
         // ---- dataflow runs: maximal runs (>= 2) of consecutive batches with at
@@ -1106,6 +1188,29 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
         constexpr bool kFlowEnabled = false;
         const bool flow_on = (kFlowEnabled || (flags & EDB_FLOW_DRYRUN)) && !(flags & EDB_NO_FLOW) &&
                              T <= FLOW_MAX_TYPES && flow_max_m > 0;
+        // ---- team launch: the tail of the schedule as one launch (team_kernel.h) ----
+        edb::TeamPlan team;
+        if (team_ok) {
+            std::vector<edb::TeamCell> tc(T);
+            for (int32_t t = 0; t < T; ++t) {
+                const KindInfo ki = kind_info(cells[t].kind);
+                tc[t] = edb::TeamCell{cells[t].kind, dims[t].G, ki.nfix, dims[t].K / dims[t].KG, ki.x, ki.rag};
+            }
+            edb::plan_teams(g, s, p, tc, dtype, H, n_cu, max_lds, bcost, team);
+        }
+        if (team.b0 >= 0 && n_x > 0 && !(flags & EDB_X_DIRECT) && !e->x_in_place) {
+            // the team launch reads the caller's x rows: with every batch that reads x
+            // inside it, nothing is staged
+            bool all = true;
+            for (int32_t b = 0; b < team.b0; ++b) all = all && !kind_info(cells[s->batch_type[b]].kind).x;
+            if (all) e->flags = flags = flags | EDB_X_DIRECT;
+        }
+        for (int32_t b = 0; b < (team.b0 < 0 ? B : team.b0); ++b)
+            if (blaunch[b].empty())
+                if (edb_status st = choose(b)) {
+                    delete e;
+                    return st;
+                }
         std::vector<int> run_of(B, -1);
         {
             int b = 0, nrun = 0;
@@ -1134,6 +1239,7 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
         std::vector<int64_t> counter_fix;   // launches whose counter offsets need the final base
         int64_t n_counters = 0;
         for (int32_t b = 0; b < B;) {
+            if (team.b0 >= 0 && b >= team.b0) break;
             if (run_of[b] < 0) {
                 for (const Launch& Lp : blaunch[b]) e->launches.push_back(Lp);
                 ++b;
@@ -1242,6 +1348,45 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             e->launches.push_back(F);
             b = b1;
         }
+        if (team.b0 >= 0) {
+            Launch F{};
+            F.team = true;
+            F.kk = -1;
+            F.info.batch = team.b0;
+            F.info.kind = -1;
+            F.info.variant = TEAM_VARIANT;
+            F.info.n_batches = B - team.b0;
+            F.info.m = s->batch_ptr[B] - s->batch_ptr[team.b0];
+            F.info.block = TEAM_NT;
+            F.info.grid = team.P * team.C;
+            F.lds = team.lds;
+            F.team_fn = team.entry.fn;
+            F.team_type[0] = team.type[0];
+            F.team_type[1] = team.type[1];
+            F.type = team.type[0] >= 0 ? team.type[0] : team.type[1];
+            F.team_P = team.P;
+            F.team_C = team.C;
+            F.team_ub = team.ub;
+            F.team_blk = team.blk_ints;
+            F.team_rows = team.rows;
+            // reloads of one wait: over a second at the 0.5 us of a reload; EDB_SPIN_US bounds it for tests
+            F.team_limit = std::getenv("EDB_SPIN_US") ? 2 * spin_us : 1 << 22;
+            F.off_x = F.off_f0 = F.off_f1 = F.off_rag = F.off_rptr = F.off_res = -1;
+            align_hb(4);
+            F.off_team = (int64_t)hb.size();
+            for (int c = 0; c < team.C; ++c) team.ints[2 * c] += (int32_t)F.off_team;
+            hb.insert(hb.end(), team.ints.begin(), team.ints.end());
+            e->off_fill = (int64_t)hb.size();
+            e->n_fill_h = (int32_t)team.fill_h.size();
+            e->n_fill_c = (int32_t)team.fill_c.size();
+            hb.insert(hb.end(), team.fill_h.begin(), team.fill_h.end());
+            hb.insert(hb.end(), team.fill_c.begin(), team.fill_c.end());
+            F.off_ticket = n_counters;
+            n_counters += 2;
+            e->team_batches.reserve(B - team.b0);
+            for (int32_t b = team.b0; b < B; ++b) e->team_batches.push_back(lists(b));
+            e->launches.push_back(F);
+        }
         // counter region: zeroed by the staging kernel before every forward
         align_hb(4);
         e->off_counters = (int64_t)hb.size();
@@ -1253,21 +1398,27 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             F.f_error += e->off_counters;
             F.f_done += e->off_counters;
         }
+        if (team.b0 >= 0) e->launches.back().off_ticket += e->off_counters;
+        const bool staging = !((flags & EDB_X_DIRECT) || e->x_in_place);
+        e->launches[0].info.grid = ((staging ? n_x : 0) + e->n_zero + e->n_fill_h + e->n_fill_c + 3) / 4;   // 4 rows per work-group
         // When the staging launch would only clear the zero and pad rows, the
         // first batch's launch clears them and the staging launch is dropped
         // (grid 0).  Only for a first batch without child lists (it then reads
         // no arena row) whose x segment has no padding columns (the staged
         // tile reads the zero row for those), run as a single launch.
-        if (e->launches.size() > 1 && n_counters == 0) {
+        if (e->launches.size() > 1 && counter_fix.empty()) {
             Launch& L1 = e->launches[1];
             const bool staged_x = !((flags & EDB_X_DIRECT) || e->x_in_place) && n_x > 0;
-            const KindInfo k1 = L1.flow ? KindInfo{} : kind_info(L1.info.kind);
-            const bool single = !L1.flow && L1.info.batch == 0 && L1.info.part == 0 && L1.kk == L1.info.kind &&
+            const KindInfo k1 = L1.flow || L1.team ? KindInfo{} : kind_info(L1.info.kind);
+            const bool single = !L1.flow && !L1.team && L1.info.batch == 0 && L1.info.part == 0 && L1.kk == L1.info.kind &&
                                 (e->launches.size() == 2 || e->launches[2].info.batch != 0);
             if (!staged_x && single && k1.G > 0 && k1.nfix == 0 && !k1.rag && dims[L1.type].Ep == dims[L1.type].E) {
                 e->launches[0].info.grid = 0;
                 L1.off_zrows = e->off_zero;
                 L1.args.n_zero = e->n_zero;
+                L1.args.n_fill_h = e->n_fill_h;
+                L1.args.n_fill_c = e->n_fill_c;
+                L1.args.nint = (int)n_counters;
             }
         }
         // dataflow grids: at most the resident work-groups (more would only exit)
@@ -1341,7 +1492,16 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             }
             for (size_t i = 1; he == hipSuccess && i < e->launches.size(); ++i) {
                 const Launch& L = e->launches[i];
-                if (L.lds <= 64 * 1024 || L.flow || L.kk < 0) continue;
+                if (L.team && L.lds > 64 * 1024) {
+                    std::lock_guard<std::mutex> lk(g_ctx_mu);
+                    int& granted = ctx->team_lds[L.team_fn];
+                    if (L.lds > granted) {
+                        he = hipFuncSetAttribute(L.team_fn, hipFuncAttributeMaxDynamicSharedMemorySize, L.lds);
+                        if (he == hipSuccess) granted = L.lds;
+                    }
+                    continue;
+                }
+                if (L.lds <= 64 * 1024 || L.flow || L.team || L.kk < 0) continue;
                 const int key = (L.kk * 2 + dtype) * NUM_VARIANTS + L.info.variant;
                 std::lock_guard<std::mutex> lk(g_ctx_mu);
                 int& granted = ctx->lds_granted[key];
@@ -1392,7 +1552,11 @@ BatchArgs resolve_args(const edb_exec* e, const Launch& L, const void* const* w,
     if (L.off_rag >= 0) a.rag.idx = db + L.off_rag;
     if (L.off_rptr >= 0) a.rag_ptr = db + L.off_rptr;
     if (L.off_res >= 0) a.res.idx = db + L.off_res;
-    if (L.off_zrows >= 0) a.zrows = db + L.off_zrows;
+    if (L.off_zrows >= 0) {
+        a.zrows = db + L.off_zrows;
+        a.frows = db + e->off_fill;
+        a.ints = e->dbuf + e->off_counters;
+    }
     return a;
 }
 
@@ -1404,7 +1568,7 @@ struct Call {
     unsigned grid = 0, block = 256;
     size_t lds = 0;               // dynamic LDS bytes
     int launch = 0;               // its launch record (EDB_PROFILE events)
-    int form = 0;                 // 0 (BatchArgs), 1 (BatchArgs, bf16*, float*), 2 (BatchArgs, T*), 3 staging, 4 dataflow
+    int form = 0;                 // 0 (BatchArgs), 1 (BatchArgs, bf16*, float*), 2 (BatchArgs, T*), 3 staging, 4 dataflow, 5 team
     BatchArgs a{};
     void* p0 = nullptr;
     void* p1 = nullptr;
@@ -1421,8 +1585,11 @@ struct Call {
         int H;
         int* ints;
         int nint;
+        const int* frow;
+        int n_fill_h, n_fill_c;
     } s{};
-    void* argv[12];
+    TeamArgs t{};
+    void* argv[15];
     // pointers to the arguments (into this object: call after it has its final address)
     void** args() {
         switch (form) {
@@ -1433,7 +1600,9 @@ struct Call {
                 argv[0] = &s.x; argv[1] = &s.xs; argv[2] = &s.src; argv[3] = &s.n_x; argv[4] = &s.E;
                 argv[5] = &s.zrow; argv[6] = &s.n_zero; argv[7] = &s.arena_h; argv[8] = &s.arena_c;
                 argv[9] = &s.H; argv[10] = &s.ints; argv[11] = &s.nint;
+                argv[12] = &s.frow; argv[13] = &s.n_fill_h; argv[14] = &s.n_fill_c;
                 break;
+            case 5: argv[0] = &t; break;
             default: argv[0] = &f; break;
         }
         return argv;
@@ -1459,7 +1628,8 @@ void build_calls(const edb_exec* e, const void* const* w, const void* x, void* a
             c.form = 3;
             c.s = Call::Stage{x, e->xstaged, db + e->off_xsrc, direct ? 0 : e->n_x, e->E, db + e->off_zero,
                               e->n_zero, arena_h, reinterpret_cast<float*>(arena_c), e->H,
-                              e->dbuf + e->off_counters, (int)e->n_counters};
+                              e->dbuf + e->off_counters, (int)e->n_counters, db + e->off_fill, e->n_fill_h,
+                              e->n_fill_c};
             out.push_back(c);
         }
     }
@@ -1493,6 +1663,37 @@ void build_calls(const edb_exec* e, const void* const* w, const void* x, void* a
                        : reinterpret_cast<const void*>(&flow_kernel<__bf16>);
             c.lds = L.lds;
             c.form = 4;
+            out.push_back(c);
+            continue;
+        }
+        if (L.team) {
+            TeamArgs& t = c.t;
+            for (int i = 0; i < 2; ++i) {
+                const int ty = L.team_type[i];
+                if (ty < 0) continue;
+                const Dims& d = e->dims[ty];
+                const uint8_t* wb = reinterpret_cast<const uint8_t*>(w[ty]);
+                t.t[i] = TeamType{reinterpret_cast<const uint4*>(wb + d.off_W), reinterpret_cast<const float*>(wb + d.off_b),
+                                  d.rag ? reinterpret_cast<const uint4*>(wb + d.off_Wr) : nullptr,
+                                  d.rag ? reinterpret_cast<const float*>(wb + d.off_br) : nullptr, d.E, d.Ep, d.Hk, d.Hu, d.K};
+            }
+            t.ibuf = db;
+            t.off_table = (int)L.off_team;
+            t.ticket = e->dbuf + L.off_ticket;
+            t.P = L.team_P;
+            t.C = L.team_C;
+            t.H = e->H;
+            t.n_slots = e->n_slots;
+            t.n_xrows = e->x_direct_rows;
+            t.blk_ints = L.team_blk;
+            t.limit = L.team_limit;
+            t.x = x;
+            t.arena_h = arena_h;
+            t.arena_c = reinterpret_cast<float*>(arena_c);
+            c.fn = L.team_fn;
+            c.block = L.info.block;
+            c.lds = L.lds;
+            c.form = 5;
             out.push_back(c);
             continue;
         }
@@ -1533,18 +1734,26 @@ void build_calls(const edb_exec* e, const void* const* w, const void* x, void* a
     }
 }
 
+// gate: the device's team launches (NULL: the caller orders its calls on the device).
 hipError_t launch_all(edb_exec* e, const void* const* w, const void* x, void* arena_h, void* arena_c,
-                      hipStream_t st) {
+                      hipStream_t st, TeamGate* gate) {
     thread_local std::vector<Call> calls;
     build_calls(e, w, x, arena_h, arena_c, calls);
     const bool prof = !e->events.empty();
     hipError_t he = hipSuccess;
     for (Call& c : calls) {
+        std::unique_lock<std::mutex> lk;
+        if (c.form == 5 && gate) {
+            lk = std::unique_lock<std::mutex>(gate->mu);
+            he = gate->enter(st);
+            if (he != hipSuccess) return he;
+        }
         if (prof)
             he = hipExtLaunchKernel(c.fn, dim3(c.grid), dim3(c.block), c.args(), c.lds, st, e->events[2 * c.launch],
                                     e->events[2 * c.launch + 1], 0);
         else
             he = hipLaunchKernel(c.fn, dim3(c.grid), dim3(c.block), c.args(), c.lds, st);
+        if (he == hipSuccess && lk.owns_lock()) he = gate->leave(st, &e->team_done);
         if (he != hipSuccess) return he;
     }
     return hipGetLastError();
@@ -1590,7 +1799,7 @@ hipKernelNodeParams node_params(Call& c) {
 // Runs the execution's calls on st through the stream's graph of the same
 // kernel sequence (instantiated on first use).
 hipError_t graph_launch(edb_exec* e, const void* const* w, const void* x, void* arena_h, void* arena_c,
-                        hipStream_t st) {
+                        hipStream_t st, TeamGate* gate) {
     int dev = 0;
     hipError_t he = hipGetDevice(&dev);
     if (he != hipSuccess) return he;
@@ -1663,7 +1872,14 @@ hipError_t graph_launch(edb_exec* e, const void* const* w, const void* x, void* 
     t->owner = e->id;
     t->owner_ptrs = ptrs;
     t->used = ++ts->tick;
+    std::unique_lock<std::mutex> glk;
+    if (!calls.empty() && calls.back().form == 5) {   // a team launch is the last of its sequence
+        glk = std::unique_lock<std::mutex>(gate->mu);
+        he = gate->enter(st);
+        if (he != hipSuccess) return he;
+    }
     he = hipGraphLaunch(t->exec, st);
+    if (he == hipSuccess && glk.owns_lock()) he = gate->leave(st, &e->team_done);
     if (he == hipSuccess) he = hipEventRecord(t->done, st);
     return he;
 }
@@ -1697,18 +1913,28 @@ extern "C" edb_status edb_execute(edb_exec_t* e, const void* const* w, const voi
     if (e->flags & EDB_DRYRUN) return EDB_OK;
     if (edb_status cs = check_exec_args(e, w, x, arena_h, arena_c, "edb_execute")) return cs;
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
-    hipError_t he = hipStreamWaitEvent(st, e->ready, 0);   // descriptors are on the device
+    hipError_t he = hipSuccess;
+    if (!e->uploaded) {   // descriptors are on the device
+        he = hipEventQuery(e->ready);
+        if (he == hipSuccess) {
+            e->uploaded = true;
+        } else if (he == hipErrorNotReady) {
+            (void)hipGetLastError();
+            he = hipStreamWaitEvent(st, e->ready, 0);
+        }
+    }
+    e->team_done = nullptr;
     if (he != hipSuccess) return fail(EDB_ERR_HIP, std::string("edb_execute: ") + hipGetErrorString(he));
     if (!(e->flags & EDB_USE_GRAPH) || (e->flags & EDB_PROFILE)) {
-        he = launch_all(e, w, x, arena_h, arena_c, st);
-        if (he == hipSuccess) he = hipEventRecord(e->done, st);
+        he = launch_all(e, w, x, arena_h, arena_c, st, e->teams.get());
+        if (he == hipSuccess && !e->team_done) he = hipEventRecord(e->done, st);
         if (he != hipSuccess) return fail(EDB_ERR_HIP, std::string("edb_execute: ") + hipGetErrorString(he));
         e->ran = true;
         e->profiled = !e->events.empty();
         return EDB_OK;
     }
-    he = graph_launch(e, w, x, arena_h, arena_c, st);
-    if (he == hipSuccess) he = hipEventRecord(e->done, st);
+    he = graph_launch(e, w, x, arena_h, arena_c, st, e->teams.get());
+    if (he == hipSuccess && !e->team_done) he = hipEventRecord(e->done, st);
     if (he != hipSuccess) return fail(EDB_ERR_HIP, std::string("edb_execute: graph: ") + hipGetErrorString(he));
     e->ran = true;
     return EDB_OK;
@@ -1730,8 +1956,10 @@ int64_t align16(int64_t v) { return (v + 15) & ~(int64_t)15; }
 const Launch* batch_launch(const edb_exec* e, int32_t b) {
     for (size_t i = 1; i < e->launches.size(); ++i) {
         const Launch& L = e->launches[i];
-        if (!L.flow && L.info.batch == b && L.info.part != 2) return &L;
+        if (!L.flow && !L.team && L.info.batch == b && L.info.part != 2) return &L;
     }
+    for (const Launch& L : e->team_batches)
+        if (L.info.batch == b) return &L;
     return nullptr;
 }
 
@@ -1909,9 +2137,10 @@ extern "C" edb_status edb_exec_check(edb_exec_t* e, void* stream) {
         he = hipMemcpy(c.data(), e->dbuf + e->off_counters, c.size() * sizeof(int32_t), hipMemcpyDeviceToHost);
     if (he != hipSuccess) return fail(EDB_ERR_HIP, std::string("edb_exec_check: ") + hipGetErrorString(he));
     for (const Launch& F : e->launches) {
-        if (!F.flow) continue;
-        if (c[F.f_error - e->off_counters] != 0)
+        if (F.flow && c[F.f_error - e->off_counters] != 0)
             return fail(EDB_ERR_HIP, "edb_exec_check: a dataflow wait timed out; results are invalid");
+        if (F.team && c[F.off_ticket + 1 - e->off_counters] != 0)
+            return fail(EDB_ERR_HIP, "edb_exec_check: a wait of the team launch timed out; results are invalid");
     }
     return EDB_OK;
 }
@@ -2129,8 +2358,8 @@ edb_status edb::forward_on_stream(const edb_graph_t* g, const edb_schedule_t* s,
             e->dbuf = reinterpret_cast<int*>(sl.dev);
             e->dmem = nullptr;
             e->dmem_owned = false;
-            he = use_graph ? graph_launch(e, packed_weights, x, arena_h, arena_c, hs)
-                           : launch_all(e, packed_weights, x, arena_h, arena_c, hs);
+            he = use_graph ? graph_launch(e, packed_weights, x, arena_h, arena_c, hs, e->teams.get())
+                           : launch_all(e, packed_weights, x, arena_h, arena_c, hs, e->teams.get());
         }
         if (he == hipSuccess) he = hipEventRecord(sl.done, hs);
         if (he == hipSuccess) {
@@ -2273,7 +2502,7 @@ extern "C" edb_status edb_forward_noalloc(int32_t n_nodes, int32_t n_types, cons
         // (the host array is read before the call returns: a copy from pageable
         // memory is staged synchronously)
         he = hipMemcpyAsync(e->dbuf, e->hbuf.data(), e->hbuf.size() * sizeof(int32_t), hipMemcpyHostToDevice, hs);
-        if (he == hipSuccess) he = launch_all(e, packed_weights, x, arena_h, arena_c, hs);
+        if (he == hipSuccess) he = launch_all(e, packed_weights, x, arena_h, arena_c, hs, nullptr);
         if (he != hipSuccess) st = fail(EDB_ERR_HIP, std::string("edb_forward_noalloc: ") + hipGetErrorString(he));
     }
     const std::string err = st == EDB_OK ? std::string() : std::string(edb_last_error());
@@ -2374,6 +2603,92 @@ bool v_batch_rows(VCheck& c, const std::vector<int32_t>& hb, const VBatch& b, in
     return true;
 }
 
+// A team launch: every team's block is decoded as the kernel reads it.  Every
+// offset and count is checked against its buffer, every row is written once,
+// and every row a tile reads was written by an earlier launch (then it is not
+// waited for) or by an earlier tile of the same team (then it is, and starts
+// out empty).
+bool v_team(VCheck& c, const edb_exec* e, const Launch& L, const std::string& what, const std::vector<uint8_t>& empty_h,
+            const std::vector<uint8_t>& empty_c, std::vector<int64_t>& written, int64_t li, int64_t& n_checked) {
+    const std::vector<int32_t>& hb = e->hbuf;
+    const int64_t n_slots = e->n_slots, ni = (int64_t)hb.size();
+    if (L.team_P < 1 || L.team_C < 1 || L.info.grid != L.team_P * L.team_C || L.info.block != TEAM_NT)
+        return c.fail(what + ": grid");
+    if (L.team_P * 16 * L.team_ub < e->H || (L.team_P - 1) * 16 * L.team_ub >= e->H) return c.fail(what + ": units");
+    if (L.off_team < 0 || L.off_team % 4 || L.off_team + 2LL * L.team_C > ni) return c.fail(what + ": table of the teams");
+    if (L.off_ticket < e->off_counters || L.off_ticket + 2 > e->off_counters + e->n_counters)
+        return c.fail(what + ": ticket outside the counter region");
+    if (L.team_limit < 1) return c.fail(what + ": wait bound");
+    std::vector<int64_t> mine((size_t)n_slots, -1);   // team that writes the row in this launch
+    int64_t total = 0;
+    for (int tm = 0; tm < L.team_C; ++tm) {
+        const std::string tw = what + " team " + std::to_string(tm);
+        const int64_t off = hb[(size_t)(L.off_team + 2 * tm)], n = hb[(size_t)(L.off_team + 2 * tm + 1)];
+        if (off < 0 || off % 4 || n < 4 || n % 4 || off + n > ni || n > L.team_blk) return c.fail(tw + ": block");
+        const int32_t* b = hb.data() + off;
+        const int64_t nt = b[0], nr = b[1], nk = b[2];
+        if (nt < 1 || nr < 1 || nk < 0 || 4 + TEAM_TILE_INTS * nt + TEAM_REC_INTS * nr + 2 * nk > n || nr > L.team_rows)
+            return c.fail(tw + ": counts");
+        const int32_t *tiles = b + 4, *rec = tiles + TEAM_TILE_INTS * nt, *kids = rec + TEAM_REC_INTS * nr;
+        total += nr;
+        std::vector<int32_t> slot_of((size_t)nr, -1);   // slots written by this team so far, by local row
+        auto reads = [&](int32_t slot, int32_t local, int64_t row0, bool via_c, const std::string& rw) {
+            if (slot < 0 || slot >= n_slots) return c.fail(rw + ": row " + std::to_string(slot) + " out of range");
+            if (local < 0) {
+                if (written[(size_t)slot] == -2) return c.fail(rw + ": reads a row that no earlier launch writes");
+                return true;
+            }
+            if (local >= row0 || slot_of[(size_t)local] != slot) return c.fail(rw + ": child is not an earlier row of the team");
+            if (!(via_c ? empty_c : empty_h)[(size_t)slot]) return c.fail(rw + ": waits for a row that does not start out empty");
+            return true;
+        };
+        int64_t next = 0, kid = 0;
+        for (int64_t t = 0; t < nt; ++t) {
+            const int32_t* h = tiles + TEAM_TILE_INTS * t;
+            const std::string rw = tw + " tile " + std::to_string(t);
+            if ((h[0] != 0 && h[0] != 1) || L.team_type[h[0]] < 0) return c.fail(rw + ": type");
+            const int ty = L.team_type[h[0]], kind = e->cells[ty].kind;
+            const KindInfo ki = kind_info(kind);
+            if (h[1] < 1 || h[1] > (h[6] ? 4 : TEAM_ROWS) || h[2] != next || next + h[1] > nr) return c.fail(rw + ": rows");
+            const int most = kind == EDB_CELL_CS_INTERNAL ? TEAM_CH : kind == EDB_CELL_LAT_CHAR ? TEAM_WORDS : 1 << 30;
+            if (h[3] != kid || h[4] < 0 || h[4] > most || kid + h[4] > nk) return c.fail(rw + ": children");
+            int widest = 0;
+            for (int i = 0; i < h[1]; ++i) {
+                const int32_t* q = rec + TEAM_REC_INTS * (next + i);
+                if (q[0] < 1 || q[0] >= n_slots || written[(size_t)q[0]] != -2 || mine[(size_t)q[0]] >= 0)
+                    return c.fail(rw + ": result row " + std::to_string(q[0]));
+                if (ki.x && (q[1] < 0 || q[1] >= e->x_direct_rows)) return c.fail(rw + ": x row");
+                for (int f = 0; f < ki.nfix; ++f)
+                    if (!reads(q[2 + f], q[4 + f], next, false, rw)) return false;
+                if (ki.rag) {
+                    if (q[6] < kid || q[7] < q[6] || q[7] > h[3] + h[4]) return c.fail(rw + ": child range");
+                    widest = std::max(widest, q[7] - q[6]);
+                    for (int64_t k = q[6]; k < q[7]; ++k)
+                        if (!reads(kids[2 * k], kids[2 * k + 1], next, kind == EDB_CELL_LAT_CHAR, rw)) return false;
+                }
+            }
+            if (ki.rag && widest > h[5]) return c.fail(rw + ": most children");
+            for (int i = 0; i < h[1]; ++i) {   // a tile's rows do not depend on each other
+                const int32_t v = rec[TEAM_REC_INTS * (next + i)];
+                if (mine[(size_t)v] >= 0) return c.fail(rw + ": writes a row twice");
+                mine[(size_t)v] = tm;
+                slot_of[(size_t)(next + i)] = v;
+                if (kind == EDB_CELL_LAT_WORD ? !empty_c[(size_t)v] : !empty_h[(size_t)v])
+                    return c.fail(rw + ": a row that does not start out empty");
+            }
+            next += h[1];
+            kid += h[4];
+            ++n_checked;
+        }
+        if (next != nr || kid != nk) return c.fail(tw + ": tiles do not cover the rows");
+    }
+    if (total != L.info.m) return c.fail(what + ": rows of the teams");
+    for (int64_t v = 0; v < n_slots; ++v)
+        if (mine[(size_t)v] >= 0) written[(size_t)v] = li;
+    n_checked += L.info.n_batches;
+    return true;
+}
+
 }  // namespace
 
 extern "C" edb_status edb_exec_validate(const edb_exec_t* e, int32_t n_workers, int64_t* checked) {
@@ -2411,8 +2726,20 @@ extern "C" edb_status edb_exec_validate(const edb_exec_t* e, int32_t n_workers, 
         return fail(EDB_ERR_INVALID, "edb_exec_validate: counter region outside the int buffer");
     for (int64_t i = 0; i < e->n_counters; ++i)
         if (hb[(size_t)(e->off_counters + i)] != 0) return fail(EDB_ERR_INVALID, "edb_exec_validate: counter not zero");
-    if (e->n_counters > 0 && e->launches[0].info.grid == 0)
-        return fail(EDB_ERR_INVALID, "edb_exec_validate: dataflow counters but no staging launch to clear them");
+    if (e->n_counters > 0 && e->launches[0].info.grid == 0 &&
+        !(e->launches.size() > 1 && e->launches[1].args.nint == e->n_counters && e->launches[1].off_zrows >= 0))
+        return fail(EDB_ERR_INVALID, "edb_exec_validate: counters but no launch to clear them");
+    // the rows that start out empty for a team launch
+    if (e->off_fill < 0 || e->n_fill_h < 0 || e->n_fill_c < 0 ||
+        e->off_fill + e->n_fill_h + e->n_fill_c > (int64_t)hb.size())
+        return fail(EDB_ERR_INVALID, "edb_exec_validate: empty-row lists outside the int buffer");
+    std::vector<uint8_t> empty_h((size_t)n_slots, 0), empty_c((size_t)n_slots, 0);
+    for (int i = 0; i < e->n_fill_h + e->n_fill_c; ++i) {
+        const int64_t r = hb[(size_t)(e->off_fill + i)];
+        if (r < 1 || r >= n_slots || written[(size_t)r] == -1)
+            return fail(EDB_ERR_INVALID, "edb_exec_validate: empty row " + std::to_string(r) + " out of range");
+        (i < e->n_fill_h ? empty_h : empty_c)[(size_t)r] = 1;
+    }
 
     auto batch_of = [&](const Launch& L) {
         VBatch b{};
@@ -2451,6 +2778,10 @@ extern "C" edb_status edb_exec_validate(const edb_exec_t* e, int32_t n_workers, 
     for (size_t li = 1; li < e->launches.size() && c.ok(); ++li) {
         const Launch& L = e->launches[li];
         const std::string what = "launch " + std::to_string(li) + " (batch " + std::to_string(L.info.batch) + ")";
+        if (L.team) {
+            if (!v_team(c, e, L, what, empty_h, empty_c, written, (int64_t)li, n_checked)) break;
+            continue;
+        }
         if (!L.flow) {
             if (L.kk < 0 || L.info.part != 0) {
                 // the parts before a batch's cell kernel read its lists; they write scratch rows only

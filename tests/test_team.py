@@ -1,0 +1,316 @@
+"""Team launches: the tail of a schedule as one launch whose work-groups keep
+their units' weights in registers and exchange h rows through the arena.
+CPU: the planned descriptors validate.  GPU: parity with the oracle at the
+edges of the kernels (widths, row remainders, absent and many children), NaN
+states, and the bounded wait."""
+import functools
+
+import numpy as np
+import pytest
+
+from oracle.compare import state_rel_err
+from oracle.evaluate import evaluate_workload
+from paper_2302_03851_amd import _lib as L
+from paper_2302_03851_amd import edb
+from paper_2302_03851_amd import workloads as WL
+
+
+def _graph(kinds, E, H, dtype, seed, op, ch, hx):
+    return WL.make_graph(kinds, E, H, op, ch, hx, seed=seed, dtype=dtype, bias_scale=0.2)
+
+
+def _chains(E, H, dtype, lengths, seed):
+    op, ch = [], []
+    for n in lengths:
+        for t in range(n):
+            op.append(0)
+            ch.append([-1 if t == 0 else len(op) - 2])
+    return _graph([WL.LSTM_CHAIN], E, H, dtype, seed, op, ch, [True] * len(op))
+
+
+def _trees(kinds, E, H, dtype, n_trees, depth, seed):
+    """Trees that grow by one leaf a level (deep schedules), with an absent
+    child now and then; three kinds: internal nodes of two types in turn."""
+    rng = np.random.default_rng(seed)
+    op, ch, hx = [], [], []
+    for t in range(n_trees):
+        op.append(0), ch.append([]), hx.append(True)
+        top = len(op) - 1
+        for d in range(depth - t % 3):
+            if rng.random() < 0.2:
+                other = -1
+            else:
+                op.append(0), ch.append([]), hx.append(True)
+                other = len(op) - 1
+            pair = [top, other] if rng.random() < 0.5 else [other, top]
+            op.append(1 if len(kinds) == 2 else 1 + (d + t) % 2), ch.append(pair), hx.append(False)
+            top = len(op) - 1
+    return _graph(kinds, E, H, dtype, seed, op, ch, hx)
+
+
+def _grids(E, H, dtype, n, R, C, seed):
+    op, ch = [], []
+    for _ in range(n):
+        base = len(op)
+        for i in range(R):
+            for j in range(C):
+                op.append(0)
+                ch.append([base + i * C + j - 1 if j else -1, base + (i - 1) * C + j if i else -1])
+    return _graph([WL.GRID], E, H, dtype, seed, op, ch, [True] * len(op))
+
+
+def _lattices(kinds, E, H, dtype, n, length, words, seed):
+    """Characters with `words` words ending at every third of them."""
+    op, ch, hx = [], [], []
+    gru = kinds[0] == WL.LGRU_EDGE
+    for _ in range(n):
+        prev, back = -1, []
+        for j in range(length):
+            ends = [back[max(0, j - 1 - k % 3)] for k in range(words)] if j and j % 3 == 0 else []
+            if gru:
+                edges = []
+                for src in [prev] + ends:
+                    op.append(0), ch.append([src]), hx.append(True)
+                    edges.append(len(op) - 1)
+                op.append(1), ch.append(edges), hx.append(False)
+            else:
+                ws = []
+                for src in ends:
+                    op.append(1), ch.append([src]), hx.append(True)
+                    ws.append(len(op) - 1)
+                op.append(0), ch.append([prev] + ws), hx.append(True)
+            prev = len(op) - 1
+            back.append(prev)
+    return _graph(kinds, E, H, dtype, seed, op, ch, hx)
+
+
+def _childsums(E, H, dtype, n, depth, wide, seed):
+    """Child-sum spines: every level has the level below and some leaves as
+    children, `wide` of them at the bottom."""
+    rng = np.random.default_rng(seed)
+    op, ch, hx = [], [], []
+    for _ in range(n):
+        top = None
+        for d in range(depth):
+            kids = [] if top is None else [top]
+            for _ in range(wide if d == 0 else int(rng.integers(0, 5))):
+                op.append(0), ch.append([]), hx.append(True)
+                kids.append(len(op) - 1)
+            op.append(1), ch.append(kids), hx.append(False)
+            top = len(op) - 1
+    return _graph([WL.CS_LEAF, WL.CS_INTERNAL], E, H, dtype, seed, op, ch, hx)
+
+
+TREE, TREE2 = [WL.NARY_LEAF, WL.NARY_INTERNAL], [WL.NARY_LEAF, WL.NARY_INTERNAL, WL.NARY_INTERNAL]
+GRU = [WL.GRU_LEAF, WL.GRU_INTERNAL]
+LAT, LGRU = [WL.LAT_CHAR, WL.LAT_WORD], [WL.LGRU_EDGE, WL.POOL_MEAN]
+P = functools.partial
+# widths: one unit block, a ragged last one, several; rows: one, up to 4 and past 4 per
+# team (both forms of the fp32 products), past a tile of 16
+CASES = {
+    "chain f32 one row": P(_chains, 16, 16, "f32", [9], 1),
+    "chain f32 H 20": P(_chains, 12, 20, "f32", [9, 7, 9], 2),
+    "chain f32 H 200": P(_chains, 100, 200, "f32", [10, 9, 9, 8, 3, 1, 7], 3),
+    "chain f32 H 512": P(_chains, 64, 512, "f32", [8] * 19, 4),
+    "chain bf16 H 264": P(_chains, 40, 264, "bf16", [9] * 21, 5),
+    "chain bf16 H 24": P(_chains, 8, 24, "bf16", [9, 2, 8], 6),
+    "tree f32 H 40": P(_trees, TREE, 28, 40, "f32", 5, 9, 7),
+    "tree f32 H 256": P(_trees, TREE, 64, 256, "f32", 23, 9, 8),
+    "tree f32 5 rows a team": P(_trees, TREE, 32, 256, "f32", 70, 8, 9),
+    "tree f32 19 rows a team": P(_trees, TREE, 32, 256, "f32", 300, 8, 29),
+    "tree f32 H 512": P(_trees, TREE, 16, 512, "f32", 3, 8, 10),
+    "tree bf16 H 320": P(_trees, TREE, 64, 320, "bf16", 9, 9, 11),
+    "tree two types f32": P(_trees, TREE2, 36, 100, "f32", 6, 9, 12),
+    "tree two types bf16": P(_trees, TREE2, 40, 104, "bf16", 6, 9, 13),
+    "treegru f32 H 72": P(_trees, GRU, 20, 72, "f32", 7, 9, 14),
+    "treegru bf16 H 512": P(_trees, GRU, 32, 512, "bf16", 4, 9, 15),
+    "grid f32 H 36": P(_grids, 20, 36, "f32", 2, 7, 5, 16),
+    "grid bf16 tall": P(_grids, 128, 256, "bf16", 1, 9, 20, 17),
+    "grid bf16 H 72": P(_grids, 24, 72, "bf16", 3, 6, 6, 18),
+    "lattice f32 H 200": P(_lattices, LAT, 100, 200, "f32", 3, 10, 2, 19),
+    "lattice f32 16 words": P(_lattices, LAT, 20, 44, "f32", 2, 10, 16, 20),
+    "lattice f32 17 words": P(_lattices, LAT, 20, 44, "f32", 2, 13, 17, 21),
+    "lattice bf16 H 88": P(_lattices, LAT, 40, 88, "bf16", 3, 10, 3, 22),
+    "lattice gru f32 H 200": P(_lattices, LGRU, 100, 200, "f32", 3, 9, 2, 23),
+    "lattice gru f32 9 edges": P(_lattices, LGRU, 16, 52, "f32", 2, 9, 8, 24),
+    "child-sum bf16 H 512": P(_childsums, 64, 512, "bf16", 3, 9, 6, 25),
+    "child-sum bf16 32 children": P(_childsums, 32, 96, "bf16", 3, 9, 32, 26),
+    "child-sum bf16 33 children": P(_childsums, 32, 96, "bf16", 3, 9, 33, 27),
+    "child-sum f32 H 100": P(_childsums, 24, 100, "f32", 5, 9, 8, 28),
+}
+
+# more words at one character than a tile holds; fp32 grids and trees: every batch runs on its own
+NO_TEAM = {"lattice f32 17 words", "grid f32 H 36"} | {n for n in CASES if n.startswith("tree") and "f32" in n}
+
+
+def _teams(f):
+    return [f.exec.launch_info(i) for i in range(f.exec.launches())
+            if f.exec.launch_info(i)["variant"] == L.TEAM_VARIANT]
+
+
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_team_descriptors_validate(name):
+    """The team launch covers a tail of the schedule, and every row, child and
+    tile of its descriptors is in range, written once and waited for exactly
+    where an earlier tile of the same team writes it."""
+    w = CASES[name]()
+    for kw in (dict(), dict(plan_mode=L.PLAN_IDENTITY), dict(plan_mode=L.PLAN_PQ)):
+        f = edb.Forward(w, flags=L.DRYRUN | L.TEAM_DRYRUN, **kw)
+        assert f.exec.validate() >= f.sched.n_batches
+        if name in NO_TEAM:
+            assert not _teams(f)
+            continue
+        (t,) = _teams(f)
+        B = f.sched.n_batches
+        assert t["batch"] + t["n_batches"] == B and t["kind"] == -1 and t["block"] == 512
+        assert t["m"] == f.sched.batch_ptr[B] - f.sched.batch_ptr[t["batch"]]
+        assert t["grid"] <= 256
+
+
+def test_team_workloads_validate():
+    for k, n in {1: None, 2: None, 3: None, 4: None, 5: 64, 6: None, 7: None, 8: 4, 9: None}.items():
+        w = WL.make_config(k, instances=n)
+        f = edb.Forward(w, flags=L.DRYRUN | L.TEAM_DRYRUN)
+        assert f.exec.validate() >= f.sched.n_batches
+        assert bool(_teams(f)) == (k in (1, 3, 5, 9)), k
+
+
+def test_team_flags():
+    """One launch per batch, forced tiles and dry runs keep batches apart."""
+    w = WL.make_config(1)
+    for fl in (0, L.TEAM_DRYRUN | L.NO_FLOW, L.TEAM_DRYRUN | L.NO_SPLIT_K, L.TEAM_DRYRUN | L.NO_LARGE):
+        assert not _teams(edb.Forward(w, flags=L.DRYRUN | fl))
+    with pytest.raises(L.EdbError) as ei:
+        edb.Forward(w, flags=L.TEAM_DRYRUN)
+    assert ei.value.status == L.EDB_ERR_INVALID
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("name", sorted(CASES))
+def test_team_parity(name):
+    """Against the oracle (1e-4 fp32, 2e-2 bf16, the library's bounds), on a
+    replay too, and bitwise the same through the one-call path and eagerly."""
+    torch = pytest.importorskip("torch")
+    w = CASES[name]()
+    f = edb.Forward(w)
+    assert bool(_teams(f)) == (name not in NO_TEAM) and f.exec.validate() >= f.sched.n_batches
+    f.run()
+    h, c = f.states()
+    f.arena_h.fill_(3.0)
+    f.arena_c.fill_(float("nan"))
+    f.run()
+    h2, c2 = f.states()
+    np.testing.assert_array_equal(h2, h)
+    np.testing.assert_array_equal(c2, c)
+    e = edb.Forward(w, flags=L.X_DIRECT | L.FORCE_GATHER)
+    e.run()
+    h3, c3 = e.states()
+    np.testing.assert_array_equal(h3, h)
+    np.testing.assert_array_equal(c3, c)
+    fc = edb.ForwardCall(w.op_type, w.child_ptr, w.child_idx, w.x_row, w.n_types, edb.operand_shapes(w), f.cells,
+                         table=edb.LATTICE_TABLE if w.kinds == LAT else None)
+    f.arena_h.fill_(5.0)
+    fc.call([b.data_ptr() for b in f.weights], f.x.data_ptr(), f.arena_h.data_ptr(), f.arena_c.data_ptr(),
+            f.arena_h.shape[0], f.stream.cuda_stream)
+    h4, _ = f.states()
+    np.testing.assert_array_equal(h4, h)
+    torch.cuda.synchronize()
+    err = state_rel_err(h, c, *evaluate_workload(w))
+    print(f"team {name}: err {err:.3e}", flush=True)
+    assert err <= (1e-4 if w.dtype == "f32" else 2e-2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_team_nan_states(dtype):
+    """Inputs with NaN (the all-ones pattern that marks an empty row among
+    them) and infinities: no wait is confused, and the states are NaN exactly
+    where one launch per batch makes them NaN."""
+    torch = pytest.importorskip("torch")
+    w = _chains(16, 48, dtype, [10, 9, 8, 8, 7], 30)
+    out = []
+    for fl in (L.USE_GRAPH, L.USE_GRAPH | L.NO_FLOW):
+        f = edb.Forward(w, flags=fl)
+        f.x[3, :] = float("nan")
+        f.x[12, 5] = float("inf")
+        bits = f.x.view(torch.int32 if dtype == "f32" else torch.int16)
+        bits[21, :] = -1
+        f.run()
+        out.append(f.states())
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(np.isnan(a), np.isnan(b))
+        ok = ~np.isnan(a)
+        np.testing.assert_allclose(a[ok], b[ok], rtol=2e-2 if dtype == "bf16" else 1e-4, atol=1e-2 if dtype == "bf16" else 1e-6)
+
+
+@pytest.mark.gpu
+def test_team_wait_bound(monkeypatch):
+    """With a bound of two reloads a wait that times out is reported, the
+    launch ends all the same, and the next executor is right."""
+    pytest.importorskip("torch")
+    w = _chains(100, 200, "f32", [12] * 6, 31)
+    monkeypatch.setenv("EDB_SPIN_US", "1")
+    f = edb.Forward(w, flags=0)
+    f.run()
+    try:
+        f.exec.check(f.stream.cuda_stream)
+    except L.EdbError as ex:
+        assert ex.status == L.EDB_ERR_HIP and "timed out" in str(ex)
+    monkeypatch.delenv("EDB_SPIN_US")
+    g = edb.Forward(w)
+    g.run()
+    h, c = g.states()
+    assert state_rel_err(h, c, *evaluate_workload(w)) <= 1e-4
+
+
+@pytest.mark.gpu
+def test_team_launches_on_many_streams():
+    """Sixteen threads with a stream each run team launches of different
+    workloads at once, executors and one-call paths in turn: no wait times
+    out (few team launches are in flight at a time) and every arena is
+    bitwise the single run's."""
+    torch = pytest.importorskip("torch")
+    import threading
+    ws = [_lattices(LAT, 100, 200, "f32", 24, 12, 2, 40), _chains(64, 256, "bf16", [12] * 40, 41),
+          _childsums(64, 512, "bf16", 24, 8, 4, 42), _lattices(LGRU, 100, 200, "f32", 20, 10, 2, 43)]
+    ref = []
+    for w in ws:
+        f = edb.Forward(w)
+        assert _teams(f)
+        f.run()
+        ref.append(f.states())
+    streams = [torch.cuda.Stream() for _ in range(16)]
+    fs, calls = [], []
+    for i, st in enumerate(streams):
+        w = ws[i % 4]
+        with torch.cuda.stream(st):
+            fs.append(edb.Forward(w, flags=L.USE_GRAPH if i % 8 < 4 else 0))
+        calls.append(edb.ForwardCall(w.op_type, w.child_ptr, w.child_idx, w.x_row, w.n_types, edb.operand_shapes(w),
+                                     fs[i].cells, table=edb.LATTICE_TABLE if w.kinds == LAT else None))
+    torch.cuda.synchronize()
+    errors = []
+
+    def work(i):
+        f = fs[i]
+        try:
+            for r in range(12):
+                if r % 3 == 2:
+                    calls[i].call([b.data_ptr() for b in f.weights], f.x.data_ptr(), f.arena_h.data_ptr(),
+                                  f.arena_c.data_ptr(), f.arena_h.shape[0], f.stream.cuda_stream)
+                else:
+                    f.run()
+        except Exception as ex:
+            errors.append(ex)
+
+    th = [threading.Thread(target=work, args=(i,)) for i in range(16)]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    assert not errors, errors
+    for i, f in enumerate(fs):
+        h, c = f.states()
+        np.testing.assert_array_equal(h, ref[i % 4][0], err_msg=f"stream {i}")
+        np.testing.assert_array_equal(c, ref[i % 4][1], err_msg=f"stream {i}")
+    for st in streams:
+        edb.ForwardCall.release_stream(st.cuda_stream)
