@@ -124,6 +124,7 @@ SMALL_VARIANTS = [(2, 4, 1), (1, 4, 1), (1, 2, 2), (1, 1, 4), (1, 1, 8), (1, 1, 
 STREAM_SHAPES = {11: (1, 4), 12: (2, 4), 13: (1, 8), 14: (1, 16)}   # streamed tile: (rows / 16, waves)
 TEAM_VARIANT = 101                                                  # team launch: the tail of the schedule in one launch
 LARGE_CLASS = {8: 0, 9: 1, 10: 2, 15: 3, 16: 4}                     # large tile: size class
+SPLIT_ROWS = {18: 64, 19: 32, 20: 16}                               # split tile (fp32 through bf16 pieces): rows
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 
@@ -145,6 +146,8 @@ def kernel_name(kind, variant, part, dtype):
     if variant in L.LARGE_VARIANTS:
         kk = "CS_FORGET" if part == 2 else ("CS_PARENT" if kind == 5 else kname)
         return f"big_kernel<{kk}, {dtype}, size class {LARGE_CLASS[variant]}>"
+    if variant in SPLIT_ROWS:
+        return f"split_kernel<{kname}, {SPLIT_ROWS[variant]} rows>"
     if variant in STREAM_SHAPES:
         return f"stream_kernel<{kname}, {dtype}, variant {variant}>"
     return f"cell_kernel<{kname}, {dtype}, variant {variant}>"
@@ -160,6 +163,8 @@ def kernel_symbol(kind, dtype, variant, part):
     from paper_2302_03851_amd import _lib as L
     if variant == L.WS_VARIANT:
         return f"edbk::ws_kernel<{kind}>"
+    if variant in SPLIT_ROWS:
+        return f"edbk::split_kernel<{kind}, {variant - 18}>"
     if variant in STREAM_SHAPES:
         rt, wk = STREAM_SHAPES[variant]
         return f"edbk::stream_kernel<{kind}, {t}, {rt}, {wk}>"

@@ -368,12 +368,18 @@ typedef struct edb_exec edb_exec_t;
  * split-K over the waves), streamed tiles (the same shapes for kinds without
  * a ragged phase, every lane loading its own operand fragments) for the many
  * small batches, the large bf16 tile (64-256 rows, both operands through LDS)
- * for batches of thousands of rows, and for bf16 x-only leaf batches of at
+ * for batches of thousands of rows, for fp32 batches of many hundreds of
+ * rows, of up to four node types, the split tile (every product as
+ * the six largest of the nine products of the operands' three bf16 pieces,
+ * accumulated in fp32: the error against exact arithmetic is not larger than
+ * that of fp32 products; each execution splits the weights first; not for
+ * grids, linear maps and the MV-RNN, and not under EDB_NO_SPLIT_K,
+ * EDB_TILE_LARGE or EDB_NO_LARGE), and for bf16 x-only leaf batches of at
  * least 8192 rows the weight-stationary tile (32 units' weights held in LDS for
  * the whole launch, 256-row tiles walked in turn; off under EDB_NO_LARGE and
  * when another variant is forced).  Without split-K (EDB_NO_SPLIT_K, and
  * always in the large and weight-stationary tiles) a batch's results do not
- * depend on the variant:
+ * depend on the variant (the split tile aside):
  * they are bitwise equal across variants, layouts and launch modes; with it,
  * variants with the same reduction split (a streamed tile and its staged
  * counterpart) are bitwise equal.  For sweeps and tests, the environment
@@ -458,7 +464,8 @@ typedef struct {
                           classes 0-4: 256, 128, 64 rows x 64 units, then 64 and 32 rows x 32
                           units, fewer rows for 5-gate cells), 11-14 streamed tiles (counterparts
                           of the small tiles 3, 6, 4, 5), 17 the weight-stationary tile
-                          (256-row tiles x 32 units, 512 threads), 100 a dataflow launch,
+                          (256-row tiles x 32 units, 512 threads), 18-20 the split tile (fp32
+                          through bf16 pieces: 64, 32, 16 rows x 64 units), 100 a dataflow launch,
                           101 a team launch */
     int32_t grid;      /* work-groups */
     int32_t block;     /* threads per work-group */

@@ -32,6 +32,7 @@ STREAM_VARIANTS = (11, 12, 13, 14)        # streamed tile: (rows / 16, waves) = 
 STREAM_STAGED = {11: 3, 12: 6, 13: 4, 14: 5}   # the staged variant with the same rows and reduction split
 PART_CELL, PART_CHILD_SUM, PART_FORGET = 0, 1, 2
 FLOW_VARIANT = 100
+SPLIT_VARIANTS = (18, 19, 20)            # split tile (fp32 through bf16 pieces)
 TEAM_VARIANT = 101                        # team launch (the tail of the schedule in one launch)
 NOALLOC_SCRATCH_BYTES = 32 << 20   # EDB_NOALLOC_SCRATCH_BYTES
 

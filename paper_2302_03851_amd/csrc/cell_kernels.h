@@ -1454,14 +1454,63 @@ __global__ __launch_bounds__(256) void flow_kernel(FlowArgs f) {
 //   rows [n_x, n_x + n_zero): arena row zrow[i] of h and c set to zero
 //   then n_fill_h rows of h and n_fill_c rows of c (listed at frow) set to the
 //   empty pattern of a team launch (every bit set)
+//   then the weight groups of `jobs`, one a wave (below)
 //   work-group 0 also clears the `nint` counters at `ints`
+
+// The weights that the split tile reads as three bf16 pieces, split once per
+// forward.  A group is 32 k of one gate and 16 units: packed [2 k-groups][64
+// lanes][16 bytes], pieces [3][64 lanes][16 bytes], lane l holding 8 k values
+// from 8 * (l / 16) of unit l % 16.  Each piece is the rest's leading 8 bits,
+// so a weight is the sum of its pieces and they share its sign.  A rest of
+// zero leaves the smallest normal value of that sign instead (2^-126):
+// infinity times the weight is then the same infinity in every product, and a
+// finite operand's product changes by less than 2^-24 of it for weights above
+// 2^-100.  Bound by memory (2.6 MB read, 3.9 MB written for 512 by 1,280);
+// made here and not when the weights are packed, whose format stays what
+// programs have stored.
+constexpr int SPLIT_TYPES = 4;            // most types with batches on the split tile
+constexpr int SPLIT_GROUP_BYTES = 3072;
+struct SplitJobs {
+    const uint4* w[SPLIT_TYPES];
+    uint4* p[SPLIT_TYPES];
+    int n[SPLIT_TYPES];                   // groups; 0: no job
+};
+
+__device__ __forceinline__ void split_weights(const uint4* __restrict__ src, uint4* __restrict__ dst, int lane) {
+    const int q = lane >> 4;
+    const int at = (q >> 1) * 64 + (q & 1) * 32 + (lane & 15);
+    const uint4 in[2] = {src[at], src[at + 16]};
+    uint32_t o[3][4] = {};
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float v = __uint_as_float((&in[i / 4].x)[i % 4]);
+        float rest = v;
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            uint32_t u = __float_as_uint(rest);
+            if (k > 0 && v != 0.f && (u & 0x7F800000u) == 0) {
+                u = (__float_as_uint(v) & 0x80000000u) | 0x00800000u;
+                rest = 0.f;
+            } else {
+                u &= 0xFFFF0000u;
+                rest = (u & 0x7F800000u) != 0x7F800000u ? rest - __uint_as_float(u) : 0.f;
+                if (v != v) u = 0x7FC00000u;
+            }
+            o[k][i / 2] |= i & 1 ? u : u >> 16;
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) dst[k * 64 + lane] = make_uint4(o[k][0], o[k][1], o[k][2], o[k][3]);
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void stage_kernel(const T* __restrict__ x, T* __restrict__ xs,
                                                     const int* __restrict__ src, int n_x, int E,
                                                     const int* __restrict__ zrow, int n_zero,
                                                     T* __restrict__ arena_h, float* __restrict__ arena_c,
                                                     int H, int* __restrict__ ints, int nint,
-                                                    const int* __restrict__ frow, int n_fill_h, int n_fill_c) {
+                                                    const int* __restrict__ frow, int n_fill_h, int n_fill_c,
+                                                    SplitJobs jobs) {
     constexpr int V = Elem<T>::VEC;
     if (blockIdx.x == 0)
         for (int i = threadIdx.x; i < nint; i += blockDim.x) ints[i] = 0;
@@ -1484,6 +1533,14 @@ __global__ __launch_bounds__(256) void stage_kernel(const T* __restrict__ x, T* 
                         : reinterpret_cast<uint4*>(arena_c + (size_t)frow[i] * H);
         const int nv = is_h ? H / V : H / 4;
         for (int c = lane; c < nv; c += 64) d[c] = make_uint4(~0u, ~0u, ~0u, ~0u);
+    } else {
+        int i = row - n_x - n_zero - n_fill_h - n_fill_c;
+#pragma unroll
+        for (int t = 0; t < SPLIT_TYPES; ++t) {
+            if (i >= 0 && i < jobs.n[t])
+                split_weights(jobs.w[t] + (size_t)i * 128, jobs.p[t] + (size_t)i * 192, lane);
+            i -= jobs.n[t];
+        }
     }
 }
 

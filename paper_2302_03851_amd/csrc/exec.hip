@@ -19,6 +19,7 @@
 
 #include "big_tile.h"
 #include "ws_tile.h"
+#include "split_tile.h"
 #include "cell_kernels.h"
 #include "diag_kernels.h"
 #include "mv_kernels.h"
@@ -37,7 +38,8 @@ constexpr int NUM_STREAM = 4;
 constexpr int FIRST_STREAM = NUM_SMALL + NUM_LARGE;
 constexpr int FIRST_NARROW = FIRST_STREAM + NUM_STREAM;   // large size classes 3-4 (variants 15-16)
 constexpr int WS_VARIANT = FIRST_NARROW + NUM_BIG_CLASSES - NUM_LARGE;   // the weight-stationary tile
-constexpr int NUM_VARIANTS = WS_VARIANT + 1;
+constexpr int FIRST_SPLIT = WS_VARIANT + 1;               // the split tile (fp32 through bf16 pieces): 64, 32, 16 rows
+constexpr int NUM_VARIANTS = FIRST_SPLIT + 3;
 // small (staged) and streamed tile variants: rows per work-group 16*RT, units
 // per work-group 16*WU, WK waves splitting the reduction (threads per
 // work-group 64*WU*WK); the large variants have no entry here
@@ -48,7 +50,13 @@ constexpr int VAR_WK[NUM_VARIANTS] = {1, 1, 2, 4, 8, 16, 4, 2, 0, 0, 0, 4, 4, 8,
 // 32*big_cu(vb) units, 256 threads (bf16 and fp32; chunks of 128 bytes of k)
 bool is_large(int v) { return (v >= NUM_SMALL && v < FIRST_STREAM) || (v >= FIRST_NARROW && v < WS_VARIANT); }
 bool is_ws(int v) { return v == WS_VARIANT; }
+bool is_split(int v) { return v >= FIRST_SPLIT && v < NUM_VARIANTS; }
 int large_class(int v) { return v < FIRST_STREAM ? v - NUM_SMALL : v - FIRST_NARROW + NUM_LARGE; }
+// its work-groups for m rows
+int64_t split_tiles(int v, int64_t m, int Hu) {
+    const int TM = 16 * split_rb(v - FIRST_SPLIT);
+    return (m + TM - 1) / TM * ((Hu + SPLIT_TU - 1) / SPLIT_TU);
+}
 int large_variant(int vb) { return vb < NUM_LARGE ? NUM_SMALL + vb : FIRST_NARROW + vb - NUM_LARGE; }
 // streamed tile variants FIRST_STREAM..: 16*RT rows x 16 units, WK waves
 bool is_stream(int v) { return v >= FIRST_STREAM && v < FIRST_NARROW; }
@@ -91,6 +99,25 @@ struct Dims {
     bool x, rag;
     int64_t off_W, off_b, off_Wr, off_br, bytes;
 };
+
+// groups of 32 k of one gate and 16 units in a cell's main weights (split tile)
+int64_t split_weight_groups(const Dims& d) { return (int64_t)(d.Hu / 16) * d.G * (d.K / 32); }
+// The least gain, by the estimates, of the first batch that makes launch 0 split
+// its type's weights: 2.6 MB of them take it about 3 us, and 4 where it would
+// otherwise be folded into the first batch.
+constexpr double kSplitPrepUs = 4.0;
+
+// fp32 kinds with a split tile.  Not the grid: its states grow along the grid
+// and carry rounding differences with them, so the order of its sums is kept;
+// not the MV-RNN's one-gate products, which memory bounds (36,096 rows of 128
+// by 64: 13.0 us either way).
+bool split_kind(int kind) {
+    switch (kind) {
+        case EDB_CELL_LSTM_CHAIN: case EDB_CELL_NARY_LEAF: case EDB_CELL_NARY_INTERNAL: case EDB_CELL_CS_LEAF:
+        case EDB_CELL_LAT_WORD: case EDB_CELL_GRU_LEAF: case EDB_CELL_GRU_INTERNAL: case EDB_CELL_LGRU_EDGE: return true;
+        default: return false;
+    }
+}
 
 edb_status cell_dims(const edb_cell* c, Dims& d) {
     if (!c) return fail(EDB_ERR_INVALID, "cell is NULL");
@@ -304,6 +331,17 @@ Entry big_entry() {
     else return {nullptr, nullptr, nullptr};
 }
 
+// the split tile (fp32; the kinds of split_kind): 24 KB of rows and a row table, static
+inline hipError_t attr_split(int) { return hipSuccess; }
+inline int lds_split(int, int) { return 26 * 1024; }
+
+template <int KIND, typename T, int SC>
+Entry split_entry() {
+    if constexpr (!Kind<KIND>::RAG && !sums_children<KIND>() && sizeof(T) == 4 && KIND != K_GRID && Kind<KIND>::G > 1)
+        return {attr_split, lds_split, reinterpret_cast<const void*>(&split_kernel<KIND, SC>)};
+    else return {nullptr, nullptr, nullptr};
+}
+
 template <int KIND, typename T, int RT, int WK>
 hipError_t attr_stream(int lds) {
     return hipFuncSetAttribute(reinterpret_cast<const void*>(&stream_kernel<KIND, T, RT, WK>),
@@ -345,6 +383,9 @@ void fill_kind(Entry* e) {
     e[15] = big_entry<KIND, T, 3>();
     e[16] = big_entry<KIND, T, 4>();
     e[WS_VARIANT] = ws_entry<KIND, T>();
+    e[FIRST_SPLIT] = split_entry<KIND, T, 0>();
+    e[FIRST_SPLIT + 1] = split_entry<KIND, T, 1>();
+    e[FIRST_SPLIT + 2] = split_entry<KIND, T, 2>();
 }
 
 // The internal kinds of a child-sum batch on the large tile have large bf16 variants only.
@@ -528,6 +569,20 @@ double large_cost(int G, int vb, int m, int K, int Hu, int dtype, int occ, int n
            (T == 1.0 ? k[7] * nch * (cpy / 86.0 + mma) : 0.0);
 }
 
+// Estimated microseconds of the split tile: a fixed term; per chunk of 32 k the
+// first tile of a CU, its load latency and its gates' weights (shared with the
+// other CUs: a term that grows until every CU has a tile); then the further
+// tiles of the busiest CU.  Least squares over 240 launches of 200-30,000 rows
+// (median error 2%, at most 12%).
+double split_cost(int v, int m, const Dims& d, int n_cu) {
+    static const double k[3][6] = {{7.38, 0.250, 0.158, 0.082, 3.01, 0.185},
+                                   {5.73, 0.196, 0.064, 0.050, 1.81, 0.120},
+                                   {4.57, 0.0, 0.088, 0.032, 1.07, 0.119}};
+    const double* c = k[v - FIRST_SPLIT];
+    const double fill = (double)split_tiles(v, m, d.Hu) / n_cu, more = std::ceil(fill) - 1, nch = d.K / 32;
+    return c[0] + nch * (c[1] + d.G * (c[2] + c[3] * std::min(1.0, fill))) + more * (c[4] + c[5] * nch * d.G);
+}
+
 // Estimated microseconds of child_reduce_kernel over m parents (fit as above).
 double child_reduce_cost(int m) { return 3.739 + 1.0300e-3 * m; }
 
@@ -650,6 +705,8 @@ struct edb_exec {
     float* fc = nullptr;              // [fc_rows][H] fp32: sigma(f_k) c_k per child
     int64_t mvu_rows = 0;             // rows of MV-RNN vector batches
     void* mvu = nullptr;              // [mvu_rows][2H] of the cells' dtype: [B a, A b]
+    std::vector<int64_t> split_off;   // per type: byte offset of its weights' bf16 pieces in wsplit, -1 without
+    uint8_t* wsplit = nullptr;        // pieces of the types with batches on the split tile, made by launch 0
     std::vector<Dims> dims;
     std::vector<edb_cell> cells;
     std::vector<Launch> launches;     // [0] = staging, then one per batch
@@ -664,7 +721,7 @@ struct edb_exec {
     bool dmem_async = true;           // allocated with hipMallocAsync
     bool dmem_owned = true;           // false: the allocation-free entry point's array
     // byte sizes of the parts of dmem (each a multiple of 256 but the last)
-    size_t d_ibytes = 0, d_xbytes = 0, d_hbytes = 0, d_rbytes = 0, d_fbytes = 0, d_mbytes = 0, d_total = 0;
+    size_t d_ibytes = 0, d_xbytes = 0, d_hbytes = 0, d_rbytes = 0, d_fbytes = 0, d_mbytes = 0, d_wbytes = 0, d_total = 0;
     int* dbuf = nullptr;
     void* xstaged = nullptr;
     hipStream_t upload = nullptr;     // the device's upload stream
@@ -715,7 +772,7 @@ struct edb_exec {
 namespace {
 
 // Sizes of the parts of an executor's device memory (descriptor ints, staged
-// x, child-sum scratch rows, MV-RNN vector rows) and their total.
+// x, child-sum scratch rows, weights' pieces, MV-RNN vector rows) and their total.
 void layout_device(edb_exec* e) {
     auto al256 = [](size_t v) { return (v + 255) / 256 * 256; };
     const size_t esz = e->dtype == EDB_F32 ? 4 : 2;
@@ -726,7 +783,7 @@ void layout_device(edb_exec* e) {
     e->d_rbytes = al256((size_t)e->hsum_rows * e->H * 4);
     e->d_fbytes = al256((size_t)e->fc_rows * e->H * 4);
     e->d_mbytes = (size_t)e->mvu_rows * 2 * e->H * esz;
-    e->d_total = e->d_ibytes + e->d_xbytes + e->d_hbytes + e->d_rbytes + e->d_fbytes + e->d_mbytes;
+    e->d_total = e->d_ibytes + e->d_xbytes + e->d_hbytes + e->d_rbytes + e->d_fbytes + e->d_wbytes + e->d_mbytes;
 }
 
 // Point the executor's device buffers into `base` (d_total bytes, 256-aligned).
@@ -743,13 +800,16 @@ void bind_device(edb_exec* e, void* base_ptr) {
     o += e->d_rbytes;
     e->fc = e->d_fbytes ? reinterpret_cast<float*>(base + o) : nullptr;
     o += e->d_fbytes;
+    e->wsplit = e->d_wbytes ? base + o : nullptr;
+    o += e->d_wbytes;
     e->mvu = e->d_mbytes ? base + o : nullptr;
 }
 
 // edb_prepare; with noalloc the executor gets no device memory, no upload and
-// no events (the caller binds it to memory of its own and uploads hbuf).
+// no events (the caller binds it to memory of its own and uploads hbuf); with
+// lean it uses no split tile and no team launch, whose device memory is extra.
 edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb_plan_t* p,
-                        const edb_cell* cells, int32_t flags, bool noalloc, edb_exec_t** out);
+                        const edb_cell* cells, int32_t flags, bool noalloc, edb_exec_t** out, bool lean = false);
 
 }  // namespace
 
@@ -761,7 +821,7 @@ extern "C" edb_status edb_prepare(const edb_graph_t* g, const edb_schedule_t* s,
 namespace {
 
 edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb_plan_t* p,
-                        const edb_cell* cells, int32_t flags, bool noalloc, edb_exec_t** out) {
+                        const edb_cell* cells, int32_t flags, bool noalloc, edb_exec_t** out, bool lean) {
     if (!out) return fail(EDB_ERR_INVALID, "edb_prepare: out is NULL");
     *out = nullptr;
     if (!g || !s || !p || !cells) return fail(EDB_ERR_INVALID, "edb_prepare: NULL argument");
@@ -972,6 +1032,8 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             }
             return L;
         };
+        std::vector<char> split_paid(T, 0);   // types whose weights launch 0 splits
+        int n_split = 0;
         // batch b's launches: its tile variant and their estimated time
         auto choose = [&](int32_t b) -> edb_status {
             const int32_t t = s->batch_type[b];
@@ -1033,6 +1095,26 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
                 const int fk = cs_large ? K_CS_PARENT : kind_id;
                 if (table().e[fk][dtype][force_var].fn) var = lvar = force_var;
                 if (cs_large && table().e[K_CS_FORGET][dtype][force_var].fn) fvar = force_var;
+            }
+            // the split tile: fp32 batches it is estimated to be faster for
+            {
+                const bool split_ok = large_ok && dtype == EDB_F32 && split_kind(kind_id) && !lean &&
+                                      (split_paid[t] || n_split < SPLIT_TYPES) && !(flags & (EDB_NO_SPLIT_K | EDB_TILE_LARGE | EDB_NO_LARGE)) &&
+                                      (!(flags & EDB_DRYRUN) || (flags & EDB_TEAM_DRYRUN));
+                for (int v = FIRST_SPLIT; split_ok && v < NUM_VARIANTS; ++v) {
+                    const Entry& en = table().e[kind_id][dtype][v];
+                    if (!en.fn || en.lds(d.K, 0) > max_lds) continue;
+                    const double c = split_cost(v, m, d, n_cu);
+                    const double prep = split_paid[t] ? 0.0 : kSplitPrepUs;
+                    if (force_var == v || (force_var < 0 && c + prep < std::min(best, lest))) {
+                        best = c;
+                        var = v;
+                    }
+                }
+                if (is_split(var) && !split_paid[t]) {
+                    split_paid[t] = 1;
+                    ++n_split;
+                }
             }
             // the weight-stationary tile for the largest x-only batches (bf16):
             // the weights of its 32 units and its row table fit the LDS, the
@@ -1138,6 +1220,9 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
                 const int ngr = std::max({8, std::min((n_cu / nut) / 8 * 8, (nrt + 7) / 8 * 8), (need + 7) / 8 * 8});
                 L.info.grid = nut * ngr;
                 L.info.block = WS_NT;
+            } else if (is_split(var)) {
+                L.info.grid = (int)((split_tiles(var, m, d.Hu) + 7) / 8 * 8);
+                L.info.block = 256;
             } else if (is_large(var)) {
                 const int TM = large_tm(d.G, large_class(var));
                 const int tiles = (m + TM - 1) / TM * (d.Hu / large_tu(large_class(var)));
@@ -1161,7 +1246,7 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
         // A batch of few rows that a team launch may take (below) is not given
         // launches of its own before that is decided; its cost is about its
         // kernel's floor (4.1 us, 3.5 more with ragged children, and its weights).
-        const bool team_ok = force_var < 0 && large_fits &&
+        const bool team_ok = force_var < 0 && large_fits && !lean &&
                              !(flags & (EDB_NO_FLOW | EDB_NO_SPLIT_K | EDB_TILE_LARGE | EDB_NO_LARGE | EDB_FLOW_DRYRUN)) &&
                              (!(flags & EDB_DRYRUN) || (flags & EDB_TEAM_DRYRUN));
         const int few = team_ok ? 4 * std::max(1, n_cu / std::max(1, (H + 15) / 16)) : 0;
@@ -1399,8 +1484,17 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             F.f_done += e->off_counters;
         }
         if (team.b0 >= 0) e->launches.back().off_ticket += e->off_counters;
+        // the weights that launch 0 splits: those of the types with a batch on the split tile
+        e->split_off.assign(T, -1);
+        int64_t split_groups = 0;
+        for (const Launch& q : e->launches)
+            if (q.kk >= 0 && !q.flow && !q.team && is_split(q.info.variant) && e->split_off[q.type] < 0) {
+                e->split_off[q.type] = split_groups * SPLIT_GROUP_BYTES;
+                split_groups += split_weight_groups(dims[q.type]);
+            }
+        e->d_wbytes = (size_t)split_groups * SPLIT_GROUP_BYTES;
         const bool staging = !((flags & EDB_X_DIRECT) || e->x_in_place);
-        e->launches[0].info.grid = ((staging ? n_x : 0) + e->n_zero + e->n_fill_h + e->n_fill_c + 3) / 4;   // 4 rows per work-group
+        e->launches[0].info.grid = (int)(((staging ? n_x : 0) + e->n_zero + e->n_fill_h + e->n_fill_c + split_groups + 3) / 4);   // 4 rows per work-group
         // When the staging launch would only clear the zero and pad rows, the
         // first batch's launch clears them and the staging launch is dropped
         // (grid 0).  Only for a first batch without child lists (it then reads
@@ -1412,7 +1506,7 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             const KindInfo k1 = L1.flow || L1.team ? KindInfo{} : kind_info(L1.info.kind);
             const bool single = !L1.flow && !L1.team && L1.info.batch == 0 && L1.info.part == 0 && L1.kk == L1.info.kind &&
                                 (e->launches.size() == 2 || e->launches[2].info.batch != 0);
-            if (!staged_x && single && k1.G > 0 && k1.nfix == 0 && !k1.rag && dims[L1.type].Ep == dims[L1.type].E) {
+            if (!staged_x && split_groups == 0 && single && k1.G > 0 && k1.nfix == 0 && !k1.rag && dims[L1.type].Ep == dims[L1.type].E) {
                 e->launches[0].info.grid = 0;
                 L1.off_zrows = e->off_zero;
                 L1.args.n_zero = e->n_zero;
@@ -1587,9 +1681,10 @@ struct Call {
         int nint;
         const int* frow;
         int n_fill_h, n_fill_c;
+        SplitJobs jobs;
     } s{};
     TeamArgs t{};
-    void* argv[15];
+    void* argv[16];
     // pointers to the arguments (into this object: call after it has its final address)
     void** args() {
         switch (form) {
@@ -1601,6 +1696,7 @@ struct Call {
                 argv[5] = &s.zrow; argv[6] = &s.n_zero; argv[7] = &s.arena_h; argv[8] = &s.arena_c;
                 argv[9] = &s.H; argv[10] = &s.ints; argv[11] = &s.nint;
                 argv[12] = &s.frow; argv[13] = &s.n_fill_h; argv[14] = &s.n_fill_c;
+                argv[15] = &s.jobs;
                 break;
             case 5: argv[0] = &t; break;
             default: argv[0] = &f; break;
@@ -1629,7 +1725,15 @@ void build_calls(const edb_exec* e, const void* const* w, const void* x, void* a
             c.s = Call::Stage{x, e->xstaged, db + e->off_xsrc, direct ? 0 : e->n_x, e->E, db + e->off_zero,
                               e->n_zero, arena_h, reinterpret_cast<float*>(arena_c), e->H,
                               e->dbuf + e->off_counters, (int)e->n_counters, db + e->off_fill, e->n_fill_h,
-                              e->n_fill_c};
+                              e->n_fill_c, SplitJobs{}};
+            int j = 0;
+            for (int t = 0; t < e->T; ++t) {
+                if (e->split_off[t] < 0) continue;
+                SplitJobs& q = c.s.jobs;
+                q.w[j] = reinterpret_cast<const uint4*>(reinterpret_cast<const uint8_t*>(w[t]) + e->dims[t].off_W);
+                q.p[j] = reinterpret_cast<uint4*>(e->wsplit + e->split_off[t]);
+                q.n[j++] = (int)split_weight_groups(e->dims[t]);
+            }
             out.push_back(c);
         }
     }
@@ -1729,7 +1833,10 @@ void build_calls(const edb_exec* e, const void* const* w, const void* x, void* a
         }
         c.fn = table().e[L.kk][e->dtype][L.info.variant].fn;
         c.block = L.info.block;
-        c.lds = is_large(L.info.variant) ? 0 : L.lds;   // the large tile's LDS is static
+        // the large and split tiles' LDS is static
+        c.lds = is_large(L.info.variant) || is_split(L.info.variant) ? 0 : L.lds;
+        if (is_split(L.info.variant))
+            a.W = e->wsplit + e->split_off[L.type];
         out.push_back(c);
     }
 }
@@ -2489,6 +2596,12 @@ extern "C" edb_status edb_forward_noalloc(int32_t n_nodes, int32_t n_types, cons
                                            " rows, the plan needs " + std::to_string(p->n_slots));
     }
     if (st == EDB_OK) st = prepare_impl(g, s, p, cells, exec_flags, true, &e);
+    if (st == EDB_OK && e->d_total > kNoAllocScratchBytes) {
+        // the fixed array may still hold what one launch of fp32 products per batch needs
+        edb_exec_free(e);
+        e = nullptr;
+        st = prepare_impl(g, s, p, cells, exec_flags, true, &e, true);
+    }
     if (st == EDB_OK) st = check_exec_args(e, packed_weights, x, arena_h, arena_c, "edb_forward_noalloc");
     if (st == EDB_OK && e->d_total > kNoAllocScratchBytes)
         st = fail(EDB_ERR_UNSUPPORTED, "edb_forward_noalloc: this mini-batch needs " + std::to_string(e->d_total) +

@@ -1,0 +1,113 @@
+"""The split tile: fp32 batches through three bf16 pieces per operand."""
+import dataclasses
+
+import numpy as np
+import pytest
+
+from oracle.compare import state_rel_err
+from oracle.evaluate import evaluate_workload
+from paper_2302_03851_amd import _lib as L
+from paper_2302_03851_amd import edb
+from paper_2302_03851_amd import workloads as WL
+
+TREE, GRU = [WL.NARY_LEAF, WL.NARY_INTERNAL], [WL.GRU_LEAF, WL.GRU_INTERNAL]
+
+
+def _pairs(kinds, E, H, n, seed, scale=0.1):
+    """n trees of two leaves (every third with an absent right child)."""
+    op, ch, hx = [], [], []
+    for t in range(n):
+        k = len(op)
+        op += [0, 0, 1]
+        ch += [[], [], [k, k + 1 if t % 3 else -1]]
+        hx += [True, True, False]
+    return WL.make_graph(kinds, E, H, op, ch, hx, seed=seed, scale=scale, bias_scale=0.2)
+
+
+def _chains(E, H, n, seed):
+    op, ch = [0] * (3 * n), [[-1] if i % 3 == 0 else [i - 1] for i in range(3 * n)]
+    return WL.make_graph([WL.LSTM_CHAIN], E, H, op, ch, [True] * (3 * n), seed=seed, bias_scale=0.2)
+
+
+def _config(k, instances, E, H):
+    """A configuration's graphs with dimensions of whole groups of 32."""
+    w, rng = WL.make_config(k, instances=instances), np.random.default_rng(k)
+    weights = [{n: np.eye(H, dtype=np.float32) if kind == WL.POOL_MEAN and len(s) == 2 and s[0] == s[1] else
+                rng.uniform(-0.1, 0.1, size=s).astype(np.float32)
+                for n, s in WL.weight_shapes(kind, E, H, w.n_children[t] or 2)} for t, kind in enumerate(w.kinds)]
+    x = rng.standard_normal(size=(w.x.shape[0], E), dtype=np.float32)
+    return dataclasses.replace(w, in_dim=E, hidden=H, weights=weights, x=x)
+
+
+# rows: under, at and past a tile of 64 and of 32; E and H of whole and of padded groups of 32
+CASES = [(_pairs, TREE, 64, 128, 31, 1), (_pairs, TREE, 24, 92, 65, 2), (_pairs, GRU, 32, 64, 64, 3),
+         (_pairs, GRU, 56, 188, 33, 4), (_chains, 60, 124, 97, 5),
+         (_pairs, [WL.CS_LEAF, WL.CS_INTERNAL], 64, 64, 20, 6), (_config, 3, 2, 96, 188),
+         (_config, 9, 2, 60, 64)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("variant", L.SPLIT_VARIANTS)
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_split_tile_precision(case, variant, monkeypatch):
+    """Forced onto every batch: within the library's fp32 bound of the oracle,
+    and no further from it than one launch of fp32 products per batch (a
+    quarter to spare: both are sums of a few hundred rounded terms)."""
+    pytest.importorskip("torch")
+    make, *args = CASES[case]
+    w = make(*args)
+    ref = evaluate_workload(w)
+    err = []
+    for v in (16, variant):
+        monkeypatch.setenv("EDB_VARIANT", str(v))
+        f = edb.Forward(w)
+        used = {f.exec.launch_info(i)["variant"] for i in range(1, f.exec.launches())}
+        assert v in used, used
+        f.run()
+        h, c = f.states()
+        err.append((state_rel_err(h, c, *ref), np.sqrt(np.sum((h - ref[0]) ** 2) + np.sum((c - ref[1]) ** 2))))
+    print(f"split variant {variant} case {case}: max {err[1][0]:.2e}, 2-norm {err[1][1]:.3e}, fp32 products "
+          f"{err[0][1]:.3e}", flush=True)
+    assert err[1][0] <= 1e-4 and err[1][1] <= 1.25 * err[0][1]
+
+
+@pytest.mark.gpu
+def test_split_tile_chosen_and_bitwise_across_layouts():
+    """The default for large fp32 batches; layouts and launch modes agree
+    bitwise, and EDB_NO_SPLIT_K and EDB_TILE_LARGE keep to fp32 products."""
+    pytest.importorskip("torch")
+    w = _pairs(TREE, 64, 256, 4000, 6)
+    f = edb.Forward(w)
+    kinds = [f.exec.launch_info(i)["variant"] for i in range(1, f.exec.launches())]
+    assert any(v in L.SPLIT_VARIANTS for v in kinds), kinds
+    f.run()
+    h, c = f.states()
+    for kw in (dict(flags=0), dict(plan_mode=L.PLAN_IDENTITY), dict(flags=L.USE_GRAPH | L.FORCE_GATHER | L.X_DIRECT)):
+        g = edb.Forward(w, **kw)
+        g.run()
+        h2, c2 = g.states()
+        np.testing.assert_array_equal(h2, h)
+        np.testing.assert_array_equal(c2, c)
+    for fl in (L.NO_SPLIT_K, L.TILE_LARGE, L.NO_LARGE):
+        g = edb.Forward(w, flags=fl)
+        assert not any(g.exec.launch_info(i)["variant"] in L.SPLIT_VARIANTS for i in range(1, g.exec.launches()))
+
+
+@pytest.mark.gpu
+def test_split_tile_not_finite(monkeypatch):
+    """Infinities, NaN and values near the ends of the fp32 range in x: the
+    states are finite and NaN where the fp32 products make them so."""
+    pytest.importorskip("torch")
+    w = _pairs(TREE, 64, 64, 40, 7)
+    out = []
+    for v in (16, L.SPLIT_VARIANTS[0]):
+        monkeypatch.setenv("EDB_VARIANT", str(v))
+        f = edb.Forward(w)
+        f.x[0, 3], f.x[5, 7], f.x[9, 1] = float("inf"), float("-inf"), float("nan")
+        f.x[12, :], f.x[20, :], f.x[30, :] = 1e38, 3e-39, -2e-30
+        f.run()
+        out.append(f.states())
+    for a, b in zip(*out):
+        np.testing.assert_array_equal(np.isnan(a), np.isnan(b))
+        ok = ~np.isnan(a)
+        np.testing.assert_allclose(a[ok], b[ok], rtol=1e-4, atol=1e-6)
