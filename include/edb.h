@@ -339,7 +339,7 @@ edb_status edb_pack_weights(const edb_cell* cell, const float* const* logical,
                             void* packed_dev, void* stream);
 
 /* ---- execution ------------------------------------------------------------ */
-#define EDB_USE_GRAPH    1  /* run the batch sequence as one HIP graph launch (graph kept per stream) */
+#define EDB_USE_GRAPH    1  /* keep the call sequence per stream: a HIP graph, or a list of few calls */
 #define EDB_DRYRUN       2  /* record the launch list only; no HIP call (CPU testing) */
 #define EDB_FORCE_GATHER 4  /* treat every CONTIG operand as indexed (ablation) */
 #define EDB_X_DIRECT     8  /* read x rows in place by x_row instead of staging them */
@@ -405,12 +405,14 @@ edb_status edb_prepare(const edb_graph_t* g, const edb_schedule_t* s, const edb_
  * every node's staged row would be its own row of x (x is then read in
  * place), or when a single batch, or only batches of the team launch, read x
  * (they then read the caller's rows by their numbers, as under EDB_X_DIRECT).  With
- * EDB_USE_GRAPH the sequence runs as one launch of a HIP graph that the
+ * EDB_USE_GRAPH a sequence of more than 32 launches runs as one launch of a HIP graph that the
  * library keeps per device and stream and reuses for every later execution
  * there, of any executor, whose sequence has the same kernels and block sizes
  * (a new input graph of the same shape of schedule): the graph's kernel nodes
  * get the new arguments, grids and LDS sizes in place, without a new
- * instantiation; up to 4 sequences per stream are kept, the least recently
+ * instantiation.  A sequence of up to 32 launches is kept in the same way as
+ * the list of its launches, issued one by one (a graph launch starts about 12 us
+ * later).  Up to 4 sequences per stream are kept, the least recently
  * used one replaced (after its last launch has run); they live until
  * edb_stream_release on the stream or the end of the process.  Kernel faults surface at the caller's next synchronisation.
  * One edb_exec_t must not run on two streams at once. */
@@ -418,8 +420,8 @@ edb_status edb_execute(edb_exec_t* e, const void* const* packed_weights, const v
                        void* arena_h, void* arena_c, void* stream);
 
 /* Graph reuse counters of the process (EDB_USE_GRAPH executions): the kernel
- * sequences instantiated as new HIP graphs, and the executions that instead
- * updated the nodes of a kept graph in place (Section 1 prices a launch;
+ * sequences newly kept (as a HIP graph or a list), and the executions that
+ * instead updated the arguments of a kept one in place (Section 1 prices a launch;
  * dynamic inputs change the graph every mini-batch, so a new input must not
  * cost a new instantiation).  Host outputs; EDB_ERR_INVALID on NULL. */
 edb_status edb_graph_stats(int64_t* instantiated, int64_t* updated);

@@ -1866,13 +1866,20 @@ hipError_t launch_all(edb_exec* e, const void* const* w, const void* x, void* ar
     return hipGetLastError();
 }
 
-// Instantiated graphs of kernel-call sequences, kept per device and stream
+// Graphs (or lists) of kernel-call sequences, kept per device and stream
 // and reused by every later execution there whose sequence has the same
 // kernels and block sizes: a new input graph updates the nodes' arguments,
 // grids and LDS in place and is not instantiated again.  Up to kTopoPerStream
 // sequences per stream; the least recently used one is replaced.  Kept for
 // the life of the process.
 constexpr int kTopoPerStream = 4;
+// A sequence of at most this many calls is kept as a list of calls, issued one
+// by one: a graph launch starts about 12 us later on the device (2 calls: 43 us
+// a pass as a graph and 30.5 as a list; 13 calls 115 and 104; 32 calls 298 and
+// 288), and so few calls (3-4 us each on the host, at least 4 on the device)
+// keep ahead of the device.  Mini-batches on 16 streams run at the same rate
+// either way (13 and 32 calls).
+constexpr size_t kListCalls = 32;
 struct Topo {
     std::vector<std::pair<const void*, unsigned>> sig;   // kernel and block size of each node
     hipGraph_t graph = nullptr;
@@ -1880,8 +1887,10 @@ struct Topo {
     std::vector<hipGraphNode_t> nodes;
     hipEvent_t done = nullptr;     // after its last launch
     uint64_t used = 0;
-    uint64_t owner = 0;            // executor (id) and pointers the nodes hold now
+    uint64_t owner = 0;            // executor (id) and pointers the nodes or calls hold now
     std::vector<const void*> owner_ptrs;
+    std::vector<Call> calls;       // a short sequence: its calls, issued one by one (no graph)
+    bool team = false;             // its last call is a team launch
 };
 struct TopoSet {
     std::mutex mu;
@@ -1903,8 +1912,8 @@ hipKernelNodeParams node_params(Call& c) {
     return p;
 }
 
-// Runs the execution's calls on st through the stream's graph of the same
-// kernel sequence (instantiated on first use).
+// Runs the execution's calls on st through the stream's graph (or list) of the
+// same kernel sequence, made on first use.
 hipError_t graph_launch(edb_exec* e, const void* const* w, const void* x, void* arena_h, void* arena_c,
                         hipStream_t st, TeamGate* gate) {
     int dev = 0;
@@ -1922,72 +1931,84 @@ hipError_t graph_launch(edb_exec* e, const void* const* w, const void* x, void* 
     ptrs.push_back(arena_h);
     ptrs.push_back(arena_c);
     ptrs.push_back(e->dbuf);
-    thread_local std::vector<Call> calls;
-    build_calls(e, w, x, arena_h, arena_c, calls);
-    std::vector<std::pair<const void*, unsigned>> sig;
-    sig.reserve(calls.size());
-    for (const Call& c : calls) sig.emplace_back(c.fn, c.block);
     std::lock_guard<std::mutex> lk(ts->mu);
     Topo* t = nullptr;
+    // the same executor with the same buffers: the nodes (or the list) already hold its calls
     for (Topo& q : ts->t)
-        if (q.sig == sig) { t = &q; break; }
-    if (t) {
-        // the same executor with the same buffers: the nodes already hold its calls
-        if (t->owner != e->id || t->owner_ptrs != ptrs) {
-            for (size_t i = 0; he == hipSuccess && i < calls.size(); ++i) {
+        if (q.owner == e->id && q.owner_ptrs == ptrs) { t = &q; break; }
+    if (!t) {
+        thread_local std::vector<Call> calls;
+        build_calls(e, w, x, arena_h, arena_c, calls);
+        std::vector<std::pair<const void*, unsigned>> sig;
+        sig.reserve(calls.size());
+        for (const Call& c : calls) sig.emplace_back(c.fn, c.block);
+        const bool list = calls.size() <= kListCalls;
+        for (Topo& q : ts->t)
+            if (q.sig == sig) { t = &q; break; }
+        if (t) {
+            t->owner = 0;   // whoever runs next after a failure sets them all
+            for (size_t i = 0; !list && he == hipSuccess && i < calls.size(); ++i) {
                 const hipKernelNodeParams np = node_params(calls[i]);
                 he = hipGraphExecKernelNodeSetParams(t->exec, t->nodes[i], &np);
             }
-            if (he != hipSuccess) {
-                t->owner = 0;   // nodes partly updated: whoever runs next sets them all
-                return he;
-            }
+            if (he != hipSuccess) return he;
             ++g_topo_updated;
+        } else {
+            if ((int)ts->t.size() >= kTopoPerStream) {
+                // replace the least recently used sequence once its last launch has run
+                size_t lru = 0;
+                for (size_t i = 1; i < ts->t.size(); ++i)
+                    if (ts->t[i].used < ts->t[lru].used) lru = i;
+                Topo& old = ts->t[lru];
+                if (old.done) (void)hipEventSynchronize(old.done);
+                if (old.exec) (void)hipGraphExecDestroy(old.exec);
+                if (old.graph) (void)hipGraphDestroy(old.graph);
+                if (old.done) (void)hipEventDestroy(old.done);
+                ts->t.erase(ts->t.begin() + lru);
+            }
+            Topo n;
+            n.sig = sig;
+            n.team = !calls.empty() && calls.back().form == 5;   // a team launch is the last of its sequence
+            if (!list) {
+                he = hipGraphCreate(&n.graph, 0);
+                n.nodes.resize(calls.size());
+                for (size_t i = 0; he == hipSuccess && i < calls.size(); ++i) {
+                    const hipKernelNodeParams np = node_params(calls[i]);
+                    he = hipGraphAddKernelNode(&n.nodes[i], n.graph, i ? &n.nodes[i - 1] : nullptr, i ? 1 : 0, &np);
+                }
+                if (he == hipSuccess) he = hipGraphInstantiate(&n.exec, n.graph, nullptr, nullptr, 0);
+                if (he == hipSuccess) he = hipEventCreateWithFlags(&n.done, hipEventDisableTiming);
+                if (he != hipSuccess) {
+                    if (n.exec) (void)hipGraphExecDestroy(n.exec);
+                    if (n.graph) (void)hipGraphDestroy(n.graph);
+                    return he;
+                }
+            }
+            ++g_topo_instantiated;
+            ts->t.push_back(std::move(n));
+            t = &ts->t.back();
         }
-    } else {
-        if ((int)ts->t.size() >= kTopoPerStream) {
-            // replace the least recently used sequence once its last launch has run
-            size_t lru = 0;
-            for (size_t i = 1; i < ts->t.size(); ++i)
-                if (ts->t[i].used < ts->t[lru].used) lru = i;
-            Topo& old = ts->t[lru];
-            if (old.done) (void)hipEventSynchronize(old.done);
-            if (old.exec) (void)hipGraphExecDestroy(old.exec);
-            if (old.graph) (void)hipGraphDestroy(old.graph);
-            if (old.done) (void)hipEventDestroy(old.done);
-            ts->t.erase(ts->t.begin() + lru);
-        }
-        Topo n;
-        n.sig = sig;
-        he = hipGraphCreate(&n.graph, 0);
-        n.nodes.resize(calls.size());
-        for (size_t i = 0; he == hipSuccess && i < calls.size(); ++i) {
-            const hipKernelNodeParams np = node_params(calls[i]);
-            he = hipGraphAddKernelNode(&n.nodes[i], n.graph, i ? &n.nodes[i - 1] : nullptr, i ? 1 : 0, &np);
-        }
-        if (he == hipSuccess) he = hipGraphInstantiate(&n.exec, n.graph, nullptr, nullptr, 0);
-        if (he == hipSuccess) he = hipEventCreateWithFlags(&n.done, hipEventDisableTiming);
-        if (he != hipSuccess) {
-            if (n.exec) (void)hipGraphExecDestroy(n.exec);
-            if (n.graph) (void)hipGraphDestroy(n.graph);
-            return he;
-        }
-        ++g_topo_instantiated;
-        ts->t.push_back(std::move(n));
-        t = &ts->t.back();
+        if (list) t->calls = calls;
+        t->owner = e->id;
+        t->owner_ptrs = ptrs;
     }
-    t->owner = e->id;
-    t->owner_ptrs = ptrs;
     t->used = ++ts->tick;
     std::unique_lock<std::mutex> glk;
-    if (!calls.empty() && calls.back().form == 5) {   // a team launch is the last of its sequence
+    auto enter = [&]() -> hipError_t {
+        if (!t->team) return hipSuccess;
         glk = std::unique_lock<std::mutex>(gate->mu);
-        he = gate->enter(st);
-        if (he != hipSuccess) return he;
+        return gate->enter(st);
+    };
+    if (t->exec) {
+        he = enter();
+        if (he == hipSuccess) he = hipGraphLaunch(t->exec, st);
     }
-    he = hipGraphLaunch(t->exec, st);
+    for (Call& c : t->calls) {
+        if (he == hipSuccess && c.form == 5) he = enter();
+        if (he == hipSuccess) he = hipLaunchKernel(c.fn, dim3(c.grid), dim3(c.block), c.args(), c.lds, st);
+    }
     if (he == hipSuccess && glk.owns_lock()) he = gate->leave(st, &e->team_done);
-    if (he == hipSuccess) he = hipEventRecord(t->done, st);
+    if (he == hipSuccess && t->done) he = hipEventRecord(t->done, st);
     return he;
 }
 
