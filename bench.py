@@ -125,6 +125,7 @@ STREAM_SHAPES = {11: (1, 4), 12: (2, 4), 13: (1, 8), 14: (1, 16)}   # streamed t
 TEAM_VARIANT = 101                                                  # team launch: the tail of the schedule in one launch
 LARGE_CLASS = {8: 0, 9: 1, 10: 2, 15: 3, 16: 4}                     # large tile: size class
 SPLIT_ROWS = {18: 64, 19: 32, 20: 16}                               # split tile (fp32 through bf16 pieces): rows
+MV_VARIANT = 21                                                     # an MV-RNN vector batch in one launch
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 
@@ -148,6 +149,8 @@ def kernel_name(kind, variant, part, dtype):
         return f"big_kernel<{kk}, {dtype}, size class {LARGE_CLASS[variant]}>"
     if variant in SPLIT_ROWS:
         return f"split_kernel<{kname}, {SPLIT_ROWS[variant]} rows>"
+    if variant == MV_VARIANT:
+        return "mv_vec_kernel"
     if variant in STREAM_SHAPES:
         return f"stream_kernel<{kname}, {dtype}, variant {variant}>"
     return f"cell_kernel<{kname}, {dtype}, variant {variant}>"
@@ -165,6 +168,8 @@ def kernel_symbol(kind, dtype, variant, part):
         return f"edbk::ws_kernel<{kind}>"
     if variant in SPLIT_ROWS:
         return f"edbk::split_kernel<{kind}, {variant - 18}>"
+    if variant == MV_VARIANT:
+        return "edbk::mv_vec_kernel"
     if variant in STREAM_SHAPES:
         rt, wk = STREAM_SHAPES[variant]
         return f"edbk::stream_kernel<{kind}, {t}, {rt}, {wk}>"

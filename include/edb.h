@@ -467,7 +467,8 @@ typedef struct {
                           units, fewer rows for 5-gate cells), 11-14 streamed tiles (counterparts
                           of the small tiles 3, 6, 4, 5), 17 the weight-stationary tile
                           (256-row tiles x 32 units, 512 threads), 18-20 the split tile (fp32
-                          through bf16 pieces: 64, 32, 16 rows x 64 units), 100 a dataflow launch,
+                          through bf16 pieces: 64, 32, 16 rows x 64 units), 21 an MV_VEC
+                          batch in one launch, 100 a dataflow launch,
                           101 a team launch */
     int32_t grid;      /* work-groups */
     int32_t block;     /* threads per work-group */
@@ -476,8 +477,10 @@ typedef struct {
     int32_t part;      /* 0: the batch's cell kernel.  A child-sum batch on the large tile runs
                           as three launches in this order: 2 the forget GEMM over its children
                           (m = children), 1 per parent the child sum of h and the sum of the
-                          children's sigma(f_k) c_k, then 0 the parents.  An MV_VEC batch runs
-                          as 1 the matrix-vector products [B a, A b], then 0 its GEMM */
+                          children's sigma(f_k) c_k, then 0 the parents.  An MV_VEC batch of
+                          more than 64 units runs as 1 the matrix-vector products
+                          [B a, A b], then 0 its GEMM; a narrower one as 0 alone (also as two
+                          under EDB_NO_SPLIT_K, EDB_TILE_LARGE, EDB_NO_LARGE and EDB_DRYRUN) */
 } edb_launch_info;
 edb_status edb_exec_launch_info(const edb_exec_t* e, int32_t i, edb_launch_info* info);
 

@@ -40,6 +40,7 @@ constexpr int FIRST_NARROW = FIRST_STREAM + NUM_STREAM;   // large size classes 
 constexpr int WS_VARIANT = FIRST_NARROW + NUM_BIG_CLASSES - NUM_LARGE;   // the weight-stationary tile
 constexpr int FIRST_SPLIT = WS_VARIANT + 1;               // the split tile (fp32 through bf16 pieces): 64, 32, 16 rows
 constexpr int NUM_VARIANTS = FIRST_SPLIT + 3;
+constexpr int MV_VARIANT = NUM_VARIANTS;                  // an MV-RNN vector batch in one launch (no table entry)
 // small (staged) and streamed tile variants: rows per work-group 16*RT, units
 // per work-group 16*WU, WK waves splitting the reduction (threads per
 // work-group 64*WU*WK); the large variants have no entry here
@@ -1142,6 +1143,20 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
                         return fail(EDB_ERR_INVALID, "edb_prepare: an MV_VEC node of batch " + std::to_string(b) +
                                                          " does not list exactly 2 * hidden matrix columns");
                     }
+                // both in one launch for cells of up to 64 units
+                if (d.H <= MV_MAX_H && force_var < 0 && !(flags & (EDB_NO_SPLIT_K | EDB_TILE_LARGE | EDB_NO_LARGE)) &&
+                    (!(flags & EDB_DRYRUN) || (flags & EDB_TEAM_DRYRUN))) {
+                    L.lds = 0;
+                    L.off_x = -1;
+                    L.args.x = Seg{S_NONE, 0, nullptr};
+                    L.info.variant = MV_VARIANT;
+                    L.info.n_batches = 1;
+                    L.info.block = 256;
+                    L.info.grid = (m + 1) / 2;
+                    blaunch[b] = {L};
+                    bcost[b] = std::min(best, lest);
+                    return EDB_OK;
+                }
                 Launch C = L;
                 C.kk = -2;
                 C.lds = 0;
@@ -1806,6 +1821,11 @@ void build_calls(const edb_exec* e, const void* const* w, const void* x, void* a
             c.fn = reinterpret_cast<const void*>(&mv_matvec_kernel<float>);
             c.form = 2;
             c.p0 = e->mvu;
+            out.push_back(c);
+            continue;
+        }
+        if (L.info.variant == MV_VARIANT) {
+            c.fn = reinterpret_cast<const void*>(&mv_vec_kernel);
             out.push_back(c);
             continue;
         }
