@@ -872,11 +872,12 @@ def main():
     # matrix-vector launch (bytes per node: the two vector children and the 2H
     # matrix columns it reads) and a mean over children through the identity
     # map (the batch's algorithmic bytes)
-    hbm_bound = dom == (WL.MV_VEC, -1, 1) or fl == 0
+    mv_rows = dom in ((WL.MV_VEC, -1, 1), (WL.MV_VEC, MV_VARIANT, 0))   # also with the GEMM in the same launch
+    hbm_bound = mv_rows or fl == 0
     if hbm_bound:
         esz_d = 2 if w.dtype == "bf16" else 4
         grp = [inf for inf in infos[1:] if (inf["kind"], inf["variant"], inf["part"]) == dom]
-        if dom == (WL.MV_VEC, -1, 1):
+        if mv_rows:
             by_launch = sum(inf["m"] for inf in grp) * (2 * w.hidden + 2) * w.hidden * esz_d / nl
         else:
             by_launch = sum(work[b][2] for inf in grp for b in range(inf["batch"], inf["batch"] + inf["n_batches"])) / nl
