@@ -141,7 +141,9 @@ __device__ __forceinline__ void split_tile(const BatchArgs& a, int tile) {
     v8bf b[BD][G][3];
     const int ubl = min(ub, nub - 1);
     auto load_w = [&](int d, int g, int c) {
-        const uint32_t base = (uint32_t)((ubl * G + g) * nch + c) * 3072u;
+        // past the last chunk: the last one again, unused (the buffer's bounds check does not
+        // hold for a scalar offset past its end)
+        const uint32_t base = (uint32_t)((ubl * G + g) * nch + min(c, nch - 1)) * 3072u;
 #pragma unroll
         for (int k = 0; k < 3; ++k)
             b[d][g][k] = __builtin_bit_cast(v8bf, __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16 + k * 1024, base, 0));
@@ -191,7 +193,7 @@ __device__ __forceinline__ void split_tile(const BatchArgs& a, int tile) {
                     split_rows(buf ^ 1);   // past the last step: zeros, unused
                     load_rows(s + 2);
                 }
-                load_w(kc % BD, g, c + BD);   // past the last chunk: unused
+                load_w(kc % BD, g, c + BD);
                 // keeps the gates apart: left alone, the scheduler sinks every load to the step's end
                 __builtin_amdgcn_sched_barrier(0);
             }
