@@ -111,3 +111,24 @@ def test_split_tile_not_finite(monkeypatch):
         np.testing.assert_array_equal(np.isnan(a), np.isnan(b))
         ok = ~np.isnan(a)
         np.testing.assert_allclose(a[ok], b[ok], rtol=1e-4, atol=1e-6)
+
+
+@pytest.mark.gpu
+def test_noalloc_fits_without_the_pieces():
+    """Trees whose weights' pieces (63 MB) exceed the allocation-free call's
+    fixed array: the call still runs, on fp32 products; the default forward
+    uses the split tile (both within 1e-5 of each other, states below 1)."""
+    torch = pytest.importorskip("torch")
+    w = _pairs(TREE, 32, 1024, 1024, 8, scale=0.02)
+    f = edb.Forward(w)
+    assert any(f.exec.launch_info(i)["variant"] in L.SPLIT_VARIANTS for i in range(1, f.exec.launches()))
+    f.run()
+    h, c = f.states()
+    fc = edb.ForwardCall(w.op_type, w.child_ptr, w.child_idx, w.x_row, w.n_types, edb.operand_shapes(w), f.cells)
+    ah, ac = torch.full_like(f.arena_h, 7.0), torch.full_like(f.arena_c, 7.0)
+    fc.call_noalloc([b.data_ptr() for b in f.weights], f.x.data_ptr(), ah.data_ptr(), ac.data_ptr(), ah.shape[0],
+                    f.stream.cuda_stream)
+    torch.cuda.synchronize()
+    s = f.plan.slot
+    np.testing.assert_allclose(ah.cpu().numpy()[s], h, rtol=1e-5, atol=1e-5)
+    np.testing.assert_allclose(ac.cpu().numpy()[s], c, rtol=1e-5, atol=1e-5)
