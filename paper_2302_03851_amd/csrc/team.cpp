@@ -90,17 +90,28 @@ void plan_teams(const edb_graph_t* g, const edb_schedule_t* s, const edb_plan_t*
             if (family_of(cells[n0].kind, n1 < 0 ? -1 : cells[n1].kind, dtype) < 0) break;
         }
         const TeamCell& c = cells[t];
+        bool fits = true;
         if (c.kind == EDB_CELL_CS_INTERNAL || c.kind == EDB_CELL_LAT_CHAR) {
             const int most = c.kind == EDB_CELL_CS_INTERNAL ? kMaxChildren : kMaxWords;
-            bool fits = true;
             for (int i = s->batch_ptr[b]; i < s->batch_ptr[b + 1] && fits; ++i) {
                 const int32_t v = p->order[i];
                 int n = 0;
                 for (int64_t k = g->child_ptr[v] + c.nfix; k < g->child_ptr[v + 1]; ++k) n += g->child_idx[k] >= 0;
                 fits = n <= most;
             }
-            if (!fits) break;
         }
+        if (c.kind == EDB_CELL_LAT_CHAR || c.kind == EDB_CELL_LAT_WORD) {
+            // Work-groups exchange a character's h and a word's c, nothing else: a word as
+            // a positional child or a character as a ragged one keeps its batch apart.
+            for (int i = s->batch_ptr[b]; i < s->batch_ptr[b + 1] && fits; ++i) {
+                const int64_t k0 = g->child_ptr[p->order[i]];
+                for (int64_t k = k0; k < g->child_ptr[p->order[i] + 1] && fits; ++k) {
+                    const int32_t ch = g->child_idx[k];
+                    fits = ch < 0 || cells[g->op_type[ch]].kind != (k < k0 + c.nfix ? EDB_CELL_LAT_WORD : EDB_CELL_LAT_CHAR);
+                }
+            }
+        }
+        if (!fits) break;
         ty[0] = n0;
         ty[1] = n1;
         first = b;

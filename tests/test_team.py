@@ -84,6 +84,32 @@ def _lattices(kinds, E, H, dtype, n, length, words, seed):
     return _graph(kinds, E, H, dtype, seed, op, ch, hx)
 
 
+def _mixed_lattices(E, H, dtype, n, length, how, seed):
+    """Lattices whose links stray from characters and words in turn: `how`
+    "char" gives a character the one two back as a ragged child, "word" ends a
+    word in a word (its positional child), "after" follows a word with a
+    character (the character's positional child)."""
+    op, ch, hx = [], [], []
+    for _ in range(n):
+        prev, back = -1, []
+        for j in range(length):
+            rag = [back[j - 2]] if how == "char" and j >= 2 else []
+            if how != "char" and j % 3 == 2:
+                op.append(1), ch.append([back[j - 2]]), hx.append(True)
+                word = len(op) - 1
+                if how == "word":
+                    op.append(1), ch.append([word]), hx.append(True)
+                    word = len(op) - 1
+                if how == "after":
+                    prev = word
+                else:
+                    rag = [word]
+            op.append(0), ch.append([prev] + rag), hx.append(True)
+            prev = len(op) - 1
+            back.append(prev)
+    return _graph(LAT, E, H, dtype, seed, op, ch, hx)
+
+
 def _childsums(E, H, dtype, n, depth, wide, seed):
     """Child-sum spines: every level has the level below and some leaves as
     children, `wide` of them at the bottom."""
@@ -131,6 +157,10 @@ CASES = {
     "lattice f32 16 words": P(_lattices, LAT, 20, 44, "f32", 2, 10, 16, 20),
     "lattice f32 17 words": P(_lattices, LAT, 20, 44, "f32", 2, 13, 17, 21),
     "lattice bf16 H 88": P(_lattices, LAT, 40, 88, "bf16", 3, 10, 3, 22),
+    "lattice f32 characters linked": P(_mixed_lattices, 100, 200, "f32", 3, 10, "char", 32),
+    "lattice bf16 characters linked": P(_mixed_lattices, 40, 88, "bf16", 3, 10, "char", 33),
+    "lattice f32 word of a word": P(_mixed_lattices, 100, 200, "f32", 3, 10, "word", 34),
+    "lattice f32 character after a word": P(_mixed_lattices, 100, 200, "f32", 3, 10, "after", 35),
     "lattice gru f32 H 200": P(_lattices, LGRU, 100, 200, "f32", 3, 9, 2, 23),
     "lattice gru f32 9 edges": P(_lattices, LGRU, 16, 52, "f32", 2, 9, 8, 24),
     "child-sum bf16 H 512": P(_childsums, 64, 512, "bf16", 3, 9, 6, 25),
@@ -139,8 +169,10 @@ CASES = {
     "child-sum f32 H 100": P(_childsums, 24, 100, "f32", 5, 9, 8, 28),
 }
 
-# more words at one character than a tile holds; fp32 grids and trees: every batch runs on its own
-NO_TEAM = {"lattice f32 17 words", "grid f32 H 36"} | {n for n in CASES if n.startswith("tree") and "f32" in n}
+# more words at one character than a tile holds; links that a lattice's team launch does not
+# exchange (only words' c and characters' h travel) up to the last batches; fp32 grids and trees: every batch runs on its own
+NO_TEAM = {"lattice f32 17 words", "lattice f32 characters linked", "lattice bf16 characters linked",
+           "lattice f32 character after a word", "grid f32 H 36"} | {n for n in CASES if n.startswith("tree") and "f32" in n}
 
 
 def _teams(f):
