@@ -27,27 +27,29 @@
 
 namespace edbk {
 
-// Pieces of the 8 values of a lane's operand fragment, rounded to nearest.
-// What is not finite stays in the first piece.
+// Pieces of the 8 values of a lane's operand fragment, rounded to nearest.  The
+// first two stay finite: a value past the largest bf16 one (finfo.min among
+// them) takes that as its first piece and leaves the rest to the others, and
+// what is not finite goes on to the last piece, whose only product is with the
+// weight's first (never zero for a weight that is not).
 __device__ __forceinline__ void split8(const uint4& lo, const uint4& hi, uint4 (&o)[3]) {
     typedef float v2f __attribute__((ext_vector_type(2)));
     typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
+    constexpr float MOST[2] = {0x1.FEp127f, 0x1p120f};   // of a finite value's first and second piece
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const uint4& s = i < 2 ? lo : hi;
         v2f v = {__uint_as_float((&s.x)[2 * (i & 1)]), __uint_as_float((&s.x)[2 * (i & 1) + 1])};
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            const v2bf b = __builtin_convertvector(v, v2bf);
+            const v2f r = k == 2 ? v : v2f{__builtin_amdgcn_fmed3f(v.x, -MOST[k & 1], MOST[k & 1]),
+                                           __builtin_amdgcn_fmed3f(v.y, -MOST[k & 1], MOST[k & 1])};
+            const v2bf b = __builtin_convertvector(r, v2bf);
             const uint32_t u = __builtin_bit_cast(uint32_t, b);
             (&o[k].x)[i] = u;
             if (k == 2) break;
             v.x -= __uint_as_float(u << 16);
             v.y -= __uint_as_float(u & 0xFFFF0000u);
-            if (k == 0) {
-                v.x = fabsf(v.x) < 0x1p127f ? v.x : 0.f;
-                v.y = fabsf(v.y) < 0x1p127f ? v.y : 0.f;
-            }
         }
     }
 }

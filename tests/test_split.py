@@ -114,6 +114,32 @@ def test_split_tile_not_finite(monkeypatch):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("variant", L.SPLIT_VARIANTS)
+def test_split_tile_ends_of_the_range(variant, monkeypatch):
+    """The lowest and the largest fp32 value, which no bf16 value reaches, on a
+    zero weight and beside each other on weights that leave a finite sum (every
+    gate saturates upwards): finite states, the fp32 products'."""
+    pytest.importorskip("torch")
+    low, top = float(np.finfo(np.float32).min), float(np.finfo(np.float32).max)
+    w = _pairs(TREE, 64, 64, 40, 9)
+    W = w.weights[0]["W"]
+    W[3, :], W[8, :], W[9, :] = 0.0, -0.05, 0.03
+    out = []
+    for v in (16, variant):
+        monkeypatch.setenv("EDB_VARIANT", str(v))
+        f = edb.Forward(w)
+        f.x[0, 3] = f.x[1, 3] = low
+        f.x[2, 3] = top
+        f.x[6, 8] = f.x[6, 9] = low
+        f.x[7, 8], f.x[9, 9], f.x[10, 9] = low, top, 3.396e38
+        f.run()
+        out.append(f.states())
+    for a, b in zip(*out):
+        assert np.isfinite(a).all()
+        np.testing.assert_allclose(b, a, rtol=1e-4, atol=1e-6)
+
+
+@pytest.mark.gpu
 def test_noalloc_fits_without_the_pieces():
     """Trees whose weights' pieces (63 MB) exceed the allocation-free call's
     fixed array: the call still runs, on fp32 products; the default forward
