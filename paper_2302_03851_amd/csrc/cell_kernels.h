@@ -1460,14 +1460,15 @@ __global__ __launch_bounds__(256) void flow_kernel(FlowArgs f) {
 // The weights that the split tile reads as three bf16 pieces, split once per
 // forward.  A group is 32 k of one gate and 16 units: packed [2 k-groups][64
 // lanes][16 bytes], pieces [3][64 lanes][16 bytes], lane l holding 8 k values
-// from 8 * (l / 16) of unit l % 16.  Each piece is the rest's leading 8 bits,
-// so a weight is the sum of its pieces and they share its sign.  A rest of
-// zero leaves the smallest normal value of that sign instead (2^-126):
-// infinity times the weight is then the same infinity in every product, and a
-// finite operand's product changes by less than 2^-24 of it for weights above
-// 2^-100.  Bound by memory (2.6 MB read, 3.9 MB written for 512 by 1,280);
-// made here and not when the weights are packed, whose format stays what
-// programs have stored.
+// from 8 * (l / 16) of unit l % 16.  Each piece is the rest rounded to nearest,
+// so that the products the tile leaves out are less than 2^-24 of a product
+// (truncated pieces: up to 2^-22.7).  Weights of 128 and more are truncated
+// instead: all their pieces have their sign, so a product that overflows has
+// no infinite part of the other sign.  An infinite weight is the last piece,
+// which meets only the rows' first (zero for a zero row only), behind a first
+// piece of 1 of its sign for infinite rows.  Bound by memory (2.6 MB read, 3.9 MB
+// written for 512 by 1,280); made here and not when the weights are packed,
+// whose format stays what programs have stored.
 constexpr int SPLIT_TYPES = 4;            // most types with batches on the split tile
 constexpr int SPLIT_GROUP_BYTES = 3072;
 struct SplitJobs {
@@ -1484,19 +1485,14 @@ __device__ __forceinline__ void split_weights(const uint4* __restrict__ src, uin
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
         const float v = __uint_as_float((&in[i / 4].x)[i % 4]);
+        const bool finite = fabsf(v) <= 0x1.FFFFFEp127f, trunc = fabsf(v) >= 128.f;
         float rest = v;
 #pragma unroll
         for (int k = 0; k < 3; ++k) {
-            uint32_t u = __float_as_uint(rest);
-            if (k > 0 && v != 0.f && (u & 0x7F800000u) == 0) {
-                u = (__float_as_uint(v) & 0x80000000u) | 0x00800000u;
-                rest = 0.f;
-            } else {
-                u &= 0xFFFF0000u;
-                rest = (u & 0x7F800000u) != 0x7F800000u ? rest - __uint_as_float(u) : 0.f;
-                if (v != v) u = 0x7FC00000u;
-            }
-            o[k][i / 2] |= i & 1 ? u : u >> 16;
+            uint32_t u = trunc ? __float_as_uint(rest) >> 16 : __builtin_bit_cast(uint16_t, (__bf16)rest);
+            if (!finite) u = k == 2 ? __builtin_bit_cast(uint16_t, (__bf16)v) : k == 1 ? 0u : (__float_as_uint(v) >> 16 & 0x8000u) | 0x3F80u;
+            else rest -= __uint_as_float(u << 16);
+            o[k][i / 2] |= i & 1 ? u << 16 : u;
         }
     }
 #pragma unroll

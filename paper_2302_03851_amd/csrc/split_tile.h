@@ -31,7 +31,8 @@ namespace edbk {
 // first two stay finite: a value past the largest bf16 one (finfo.min among
 // them) takes that as its first piece and leaves the rest to the others, and
 // what is not finite goes on to the last piece, whose only product is with the
-// weight's first (never zero for a weight that is not).
+// weight's first (never zero for a weight that is not).  Products past 2^136 are
+// infinite or NaN, where fp32's are infinite.
 __device__ __forceinline__ void split8(const uint4& lo, const uint4& hi, uint4 (&o)[3]) {
     typedef float v2f __attribute__((ext_vector_type(2)));
     typedef __bf16 v2bf __attribute__((ext_vector_type(2)));

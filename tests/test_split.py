@@ -140,6 +140,34 @@ def test_split_tile_ends_of_the_range(variant, monkeypatch):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("variant", L.SPLIT_VARIANTS)
+def test_split_tile_infinite_weights(variant, monkeypatch):
+    """Infinite, NaN and the largest weights, of the leaves (x, infinite among
+    it) and of their parents (h): NaN where the fp32 products are, the same
+    states elsewhere."""
+    pytest.importorskip("torch")
+    inf, top = float("inf"), float(np.finfo(np.float32).max)
+    w = _pairs(TREE, 64, 64, 40, 10)
+    W, U = w.weights[0]["W"], w.weights[1]["W"]
+    W[5, 70:80], W[6, 150:160], W[7, 3], W[9, 130], W[10, 20] = inf, -inf, float("nan"), top, -300.7
+    U[3, 5], U[80, 200], U[100, 9], U[101, 10] = inf, -inf, top, -top
+    out = []
+    for v in (16, variant):
+        monkeypatch.setenv("EDB_VARIANT", str(v))
+        f = edb.Forward(w)
+        f.x[:, 5:12] = f.x[:, 5:12].abs() + 0.1   # the leaves' saturated gates are open, their tanh is 1
+        f.x[:, 6] *= -1
+        f.x[4, 5], f.x[8, 6], f.x[12, 10], f.x[16, 30] = 0.0, inf, -inf, inf
+        f.run()
+        out.append(f.states())
+    for a, b in zip(*out):
+        assert np.isnan(a).any() and np.isfinite(a).sum() > a.size // 4
+        np.testing.assert_array_equal(np.isnan(b), np.isnan(a))
+        ok = ~np.isnan(a)
+        np.testing.assert_allclose(b[ok], a[ok], rtol=1e-4, atol=1e-6)
+
+
+@pytest.mark.gpu
 def test_noalloc_fits_without_the_pieces():
     """Trees whose weights' pieces (63 MB) exceed the allocation-free call's
     fixed array: the call still runs, on fp32 products; the default forward
