@@ -371,8 +371,10 @@ typedef struct edb_exec edb_exec_t;
  * for batches of thousands of rows, for fp32 batches of many hundreds of
  * rows, of up to four node types, the split tile (every product as
  * the six largest of the nine products of the operands' three bf16 pieces,
- * accumulated in fp32: the error against exact arithmetic is not larger than
- * that of fp32 products; each execution splits the weights first; not for
+ * accumulated in fp32, the small ones apart: less than 2^-24 of a product is
+ * left out, and the states' 2-norm error against 64 bits measured at or below
+ * that of fp32 products for dense rows and for rows with few non-zeros; products
+ * past 2^136 may be NaN where fp32's are infinite; each execution splits the weights first; not for
  * grids, linear maps and the MV-RNN, and not under EDB_NO_SPLIT_K,
  * EDB_TILE_LARGE or EDB_NO_LARGE), and for bf16 x-only leaf batches of at
  * least 8192 rows the weight-stationary tile (32 units' weights held in LDS for

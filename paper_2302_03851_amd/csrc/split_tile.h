@@ -15,12 +15,22 @@
 // pieces are what the waves share: each wave splits its part of the chunk after
 // next once and hands it round through the LDS in operand order (16 bytes a
 // lane in a row: no bank conflicts).  Bound by the matrix instructions (10,247
-// rows of 512 by 1,280: 70 us, 1,150 TFLOP/s of bf16 products, the rate of a
+// rows of 512 by 1,280: 75 us, 1,075 TFLOP/s of bf16 products, the rate of a
 // large bf16 matrix product on this card), and for fewer rows than fill the CUs
 // by a work-group's own chain of loads, 22, 13 and 11 us for 64, 32 and 16 rows
 // of that size.  Against the fp32 products of the large and streamed tiles, us:
-// 10,247 rows 167 and 70, 4,075 rows 53 and 31, 2,019 rows 30 and 18, 790 rows
-// 16.5 and 13.6, 30,842 rows of 256 by 768 131 and 70.
+// 10,247 rows 167 and 75, 4,075 rows 53 and 32, 2,019 rows 30 and 19, 790 rows
+// 16.5 and 13.6, 30,842 rows of 256 by 768 131 and 75.
+//
+// Rounding: six products a term into one running total would round it six times
+// where an fp32 product rounds it once, which shows where few terms of a row are
+// not zero (16 of 512: 2-norm error 1.62e-7 for 1.08e-7).  So the five small
+// products add up in accumulators of their own, a 256th of the total's size and
+// below its rounding, and the total takes one product a chunk: 16 of 512 0.87e-7,
+// one of 512 0.78e-7 for 0.78e-7, dense rows 1.1e-7 for 3.5e-7.  Five gates over 64
+// rows have no registers for that: there a chunk's six products are summed from
+// zero and join the total by an addition (its kinds read no x; dense 1.0e-7).
+// The price is 7% of the large launches (70 to 75 us at 10,247 rows).
 #pragma once
 
 #include "cell_kernels.h"
@@ -71,6 +81,9 @@ __device__ __forceinline__ void split_tile(const BatchArgs& a, int tile) {
     // chunks of weights ahead: 16 rows have less matrix time to hide a load's; 32 rows lose by the
     // second set of registers (2,019 rows of 512 by 1,280: 18.9 us for 18.3)
     constexpr int BD = RB == 1 ? 2 : 1;
+    // the small products in accumulators of their own (where the registers hold them), else
+    // each chunk's products summed before they join the total
+    constexpr bool LOW = G * RB <= 16;
     constexpr uint32_t OOB = 0x80000000u;
     static_assert(!KT::RAG && NSEG >= 1 && RB <= 4, "positional kinds");
     __shared__ __align__(16) uint4 rows[2][KC][RB][3][64];
@@ -158,13 +171,15 @@ __device__ __forceinline__ void split_tile(const BatchArgs& a, int tile) {
         asm volatile("" ::: "memory");
     };
 
-    v4f acc[G][RB];
+    v4f acc[G][RB], low[LOW ? G : 1][RB];
 #pragma unroll
     for (int g = 0; g < G; ++g)
 #pragma unroll
-        for (int rb = 0; rb < RB; ++rb) acc[g][rb] = v4f{0.f, 0.f, 0.f, 0.f};
+        for (int rb = 0; rb < RB; ++rb) acc[g][rb] = low[LOW ? g : 0][rb] = v4f{0.f, 0.f, 0.f, 0.f};
 
-    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};   // smallest first
+    // smallest first; with sums of their own, in the order that frees the weights for their next load
+    constexpr int PA[6] = {LOW ? 0 : 2, LOW ? 1 : 0, LOW ? 0 : 1, LOW ? 2 : 1, LOW ? 1 : 0, 0};
+    constexpr int PB[6] = {LOW ? 2 : 0, LOW ? 1 : 2, 1, 0, LOW ? 0 : 1, 0};
     load_rows(0);
 #pragma unroll
     for (int d = 0; d < BD; ++d)
@@ -185,13 +200,20 @@ __device__ __forceinline__ void split_tile(const BatchArgs& a, int tile) {
             for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
                 for (int k = 0; k < 3; ++k) f[rb][k] = __builtin_bit_cast(v8bf, rows[buf][kc][rb][k][lane]);
+            v4f sums[2][RB];
 #pragma unroll
             for (int g = 0; g < G; ++g) {
 #pragma unroll
                 for (int t = 0; t < 6; ++t)
 #pragma unroll
-                    for (int rb = 0; rb < RB; ++rb)
-                        acc[g][rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[rb][PA[t]], b[kc % BD][g][PB[t]], acc[g][rb], 0, 0, 0);
+                    for (int rb = 0; rb < RB; ++rb) {
+                        v4f& d = !LOW ? sums[g & 1][rb] : t < 5 ? low[g][rb] : acc[g][rb];
+                        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[rb][PA[t]], b[kc % BD][g][PB[t]],
+                                                                    LOW || t ? d : v4f{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
+                    }
+                if (!LOW && g > 0)
+#pragma unroll
+                    for (int rb = 0; rb < RB; ++rb) acc[g - 1][rb] += sums[(g - 1) & 1][rb];
                 if (kc == 0 && g == G - 1) {
                     split_rows(buf ^ 1);   // past the last step: zeros, unused
                     load_rows(s + 2);
@@ -200,6 +222,9 @@ __device__ __forceinline__ void split_tile(const BatchArgs& a, int tile) {
                 // keeps the gates apart: left alone, the scheduler sinks every load to the step's end
                 __builtin_amdgcn_sched_barrier(0);
             }
+            if (!LOW)
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) acc[G - 1][rb] += sums[(G - 1) & 1][rb];
         }
         barrier();
     }
@@ -233,7 +258,7 @@ __device__ __forceinline__ void split_tile(const BatchArgs& a, int tile) {
         for (int i = 0; i < 4; ++i) {
             float z[G], cp[NFX > 0 ? NFX : 1], c, h;
 #pragma unroll
-            for (int g = 0; g < G; ++g) z[g] = acc[g][rb][i] + bz[g];
+            for (int g = 0; g < G; ++g) z[g] = (LOW ? acc[g][rb][i] + low[g][rb][i] : acc[g][rb][i]) + bz[g];
             cp[0] = 0.f;
 #pragma unroll
             for (int p = 0; p < NCR; ++p) cp[p] = cc[p][rb][i];

@@ -51,8 +51,7 @@ CASES = [(_pairs, TREE, 64, 128, 31, 1), (_pairs, TREE, 24, 92, 65, 2), (_pairs,
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_split_tile_precision(case, variant, monkeypatch):
     """Forced onto every batch: within the library's fp32 bound of the oracle,
-    and no further from it than one launch of fp32 products per batch (a
-    quarter to spare: both are sums of a few hundred rounded terms)."""
+    and no further from it than one launch of fp32 products per batch."""
     pytest.importorskip("torch")
     make, *args = CASES[case]
     w = make(*args)
@@ -68,7 +67,41 @@ def test_split_tile_precision(case, variant, monkeypatch):
         err.append((state_rel_err(h, c, *ref), np.sqrt(np.sum((h - ref[0]) ** 2) + np.sum((c - ref[1]) ** 2))))
     print(f"split variant {variant} case {case}: max {err[1][0]:.2e}, 2-norm {err[1][1]:.3e}, fp32 products "
           f"{err[0][1]:.3e}", flush=True)
-    assert err[1][0] <= 1e-4 and err[1][1] <= 1.25 * err[0][1]
+    assert err[1][0] <= 1e-4 and err[1][1] <= err[0][1]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("nonzero", [1, 2, 4, 16, 64])
+@pytest.mark.parametrize("kinds", [TREE, GRU, [WL.LSTM_CHAIN]])
+def test_split_tile_sparse_rows(kinds, nonzero, monkeypatch):
+    """Rows of x with few non-zeros (one-hot, masked), without biases: no
+    further from the oracle than fp32 products.  With one non-zero both round
+    once and the pieces leave out another sixth of that (1.5% of a 2-norm);
+    the norms of 3,840 states differ by 2% from sample to sample: 1.05."""
+    pytest.importorskip("torch")
+    if kinds == [WL.LSTM_CHAIN]:
+        w = _chains(512, 64, 20, 11)
+        for n in w.weights[0]:
+            w.weights[0][n] *= 5.0
+    else:
+        w = _pairs(kinds, 512, 64, 100, 11, scale=0.5)
+    rng = np.random.default_rng(nonzero)
+    for row in w.x:
+        row[rng.permutation(512)[nonzero:]] = 0.0
+    for d in w.weights:
+        for n in d:
+            if n.startswith("b"):
+                d[n][:] = 0.0
+    ref = evaluate_workload(w)
+    err = []
+    for v in (16,) + L.SPLIT_VARIANTS:
+        monkeypatch.setenv("EDB_VARIANT", str(v))
+        f = edb.Forward(w)
+        f.run()
+        h, c = f.states()
+        err.append(np.sqrt(np.sum((h - ref[0]) ** 2) + np.sum((c - ref[1]) ** 2)))
+    print(f"split kinds {kinds} nonzero {nonzero}: fp32 {err[0]:.3e}, split {err[1]:.3e} {err[2]:.3e} {err[3]:.3e}", flush=True)
+    assert max(err[1:]) <= 1.05 * err[0]
 
 
 @pytest.mark.gpu
