@@ -616,20 +616,20 @@ int best_large(int kk, int dtype, int G, int m, int K, int Hu, int n_cu, int max
 // most 2 of an XCD's 32 CUs for teams of up to 16 work-groups and 4 for teams of
 // 32.  With enough launches in flight these could fill an XCD on which every one
 // of them waits for room (seen at 16 streams).  So a launch first waits for the
-// one kTeamsInFlight launches earlier, unless that ran on its own stream: 4
-// launches hold at most 16 CUs of an XCD, which leaves room for more of them
-// from other processes.
+// one kTeamsInFlight launches earlier: 4 launches hold at most 16 CUs of an XCD,
+// which leaves room for more of them from other processes.  It waits whatever
+// stream that ran on: a handle does not tell (hipStreamPerThread is one for a
+// stream of every thread, a destroyed stream's can come back), and the runtime
+// drops a wait that the stream's own order makes needless.
 constexpr int kTeamsInFlight = 4;
 struct TeamGate {
     std::mutex mu;
     hipEvent_t done[kTeamsInFlight] = {};     // after the launch; kept for the process
-    hipStream_t stream[kTeamsInFlight] = {};
     int next = 0;
 
     // with mu held, before and after the launch on st
     hipError_t enter(hipStream_t st) {
         if (!done[next]) return hipEventCreateWithFlags(&done[next], hipEventDisableTiming);
-        if (stream[next] == st) return hipSuccess;
         const hipError_t q = hipEventQuery(done[next]);
         if (q != hipErrorNotReady) return q;
         (void)hipGetLastError();
@@ -638,7 +638,6 @@ struct TeamGate {
     hipError_t leave(hipStream_t st, hipEvent_t* last) {
         const hipError_t he = hipEventRecord(done[next], st);
         *last = done[next];
-        stream[next] = st;
         next = (next + 1) % kTeamsInFlight;
         return he;
     }

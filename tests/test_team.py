@@ -346,3 +346,44 @@ def test_team_launches_on_many_streams():
         np.testing.assert_array_equal(c, ref[i % 4][1], err_msg=f"stream {i}")
     for st in streams:
         edb.ForwardCall.release_stream(st.cuda_stream)
+
+
+@pytest.mark.gpu
+def test_team_launches_on_per_thread_streams():
+    """hipStreamPerThread is one handle for a stream of every thread: eight
+    threads run team launches through it, and free executors while the others
+    run.  Every arena is bitwise the single run's, no wait times out."""
+    torch = pytest.importorskip("torch")
+    import threading
+    w = _chains(64, 256, "bf16", [12] * 40, 44)
+    ref = edb.Forward(w)
+    assert _teams(ref)
+    ref.run()
+    h, c = ref.states()
+    fs = [[edb.Forward(w, flags=0) for _ in range(3)] for _ in range(8)]
+    torch.cuda.synchronize()
+    errors = []
+
+    def work(mine):
+        try:
+            for r in range(9):
+                f = mine[r % 3]
+                f.exec.execute([b.data_ptr() for b in f.weights], f.x.data_ptr(), f.arena_h.data_ptr(),
+                               f.arena_c.data_ptr(), 2)
+            for f in mine[:2]:
+                f.exec = None          # freed behind its launches
+            mine[2].exec.check(2)      # this thread's stream
+        except Exception as ex:
+            errors.append(ex)
+
+    th = [threading.Thread(target=work, args=(q,)) for q in fs]
+    for t in th:
+        t.start()
+    for t in th:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors, errors
+    s = ref.plan.slot
+    for f in sum(fs, []):
+        np.testing.assert_array_equal(f.arena_h.float().cpu().numpy()[s], h)
+        np.testing.assert_array_equal(f.arena_c.cpu().numpy()[s], c)
