@@ -440,9 +440,12 @@ edb_status edb_graph_stats(int64_t* instantiated, int64_t* updated);
  * node) with LAT_WORD, and LGRU_EDGE with POOL_MEAN, within the sizes that fit
  * the registers and the LDS; not under EDB_NO_FLOW, EDB_NO_SPLIT_K,
  * EDB_TILE_LARGE, EDB_NO_LARGE or a forced variant.  A row's states do not
- * depend on how rows were dealt.  Waits between work-groups are bounded (over
- * a second; the environment variable EDB_SPIN_US shortens them for tests):
- * edb_exec_check reports one that timed out.
+ * depend on how rows were dealt.  A team whose last work-group does not start
+ * within 10 ms of another (the CUs are held by other work, another process's
+ * team launches among it) is walked by that one alone, with the same results;
+ * the environment variable EDB_SPIN_US sets that time in microseconds for tests.
+ * In a team whose work-groups all run every wait ends; each is bounded all the
+ * same (over a second), and edb_exec_check reports one that ended at its bound.
  *
  * Dataflow launches (a persistent kernel running a run of consecutive small
  * batches, each tile waiting only for the tiles that produce its operand

@@ -453,8 +453,8 @@ struct Launch {
     bool team = false;
     const void* team_fn = nullptr;
     int team_type[2] = {-1, -1};
-    int team_P = 0, team_C = 0, team_ub = 1, team_blk = 0, team_limit = 0, team_rows = 0;
-    int64_t off_team = -1, off_ticket = -1;   // table of the teams' blocks; {ticket, error}
+    int team_P = 0, team_C = 0, team_ub = 1, team_blk = 0, team_limit = 0, team_attend = 0, team_rows = 0;
+    int64_t off_team = -1, off_ticket = -1;   // table of the teams' blocks; {ticket, error, states}
 };
 
 constexpr int FLOW_VARIANT = 100;
@@ -611,34 +611,51 @@ int best_large(int kk, int dtype, int G, int m, int K, int Hu, int n_cu, int max
 }  // namespace
 
 // Team launches in flight per device.  A team launch whose work-groups are not
-// all running holds the CUs of a last, incomplete team until its other members
-// find room: at most P - 1 work-groups, dealt round-robin to the 8 XCDs, so at
-// most 2 of an XCD's 32 CUs for teams of up to 16 work-groups and 4 for teams of
-// 32.  With enough launches in flight these could fill an XCD on which every one
-// of them waits for room (seen at 16 streams).  So a launch first waits for the
-// one kTeamsInFlight launches earlier: 4 launches hold at most 16 CUs of an XCD,
-// which leaves room for more of them from other processes.  It waits whatever
-// stream that ran on: a handle does not tell (hipStreamPerThread is one for a
-// stream of every thread, a destroyed stream's can come back), and the runtime
-// drops a wait that the stream's own order makes needless.
-constexpr int kTeamsInFlight = 4;
+// all running holds the CUs of its last, incomplete team until the other members
+// find room: at most P - 1 work-groups.  They can all sit on one XCD (on the one
+// that started the launch last, say, while the others' teams are complete and
+// done), and one XCD has 32 CUs with room for one such work-group each: with 32
+// held by several launches none of which is complete, each would wait for room.
+// The kernel gets out of that by itself (team_kernel.h), slowly; so that it does
+// not happen within a process, the launches in flight may hold at most 31: there
+// are four places, and a launch takes one of them for teams of up to 8
+// work-groups, two for 16 and all four for 32, and first waits for the launches
+// that had them last.  It waits whatever stream those ran on: a handle does not
+// tell (hipStreamPerThread is one for a stream of every thread, a destroyed
+// stream's can come back), and the runtime drops a wait that the stream's own
+// order makes needless.
 struct TeamGate {
+    static constexpr int PLACES = 4;
     std::mutex mu;
-    hipEvent_t done[kTeamsInFlight] = {};     // after the launch; kept for the process
+    hipEvent_t done[PLACES] = {};     // kept for the process
+    int last[PLACES] = {-1, -1, -1, -1};   // event of the last launch at each place
     int next = 0;
 
-    // with mu held, before and after the launch on st
-    hipError_t enter(hipStream_t st) {
-        if (!done[next]) return hipEventCreateWithFlags(&done[next], hipEventDisableTiming);
-        const hipError_t q = hipEventQuery(done[next]);
-        if (q != hipErrorNotReady) return q;
-        (void)hipGetLastError();
-        return hipStreamWaitEvent(st, done[next], 0);
+    static int places(int P) { return P <= 8 ? 1 : P <= 16 ? 2 : PLACES; }
+    // with mu held, before and after the launch on st of teams of P
+    hipError_t enter(hipStream_t st, int P) {
+        if (!done[next])
+            if (hipError_t he = hipEventCreateWithFlags(&done[next], hipEventDisableTiming)) return he;
+        for (int i = 0, waited = -1; i < places(P); ++i) {
+            const int ev = last[(next + i) % PLACES];
+            if (ev < 0 || ev == waited) continue;
+            waited = ev;
+            hipError_t he = hipEventQuery(done[ev]);
+            if (he == hipErrorNotReady) {
+                (void)hipGetLastError();
+                he = hipStreamWaitEvent(st, done[ev], 0);
+            }
+            if (he != hipSuccess) return he;
+        }
+        return hipSuccess;
     }
-    hipError_t leave(hipStream_t st, hipEvent_t* last) {
+    hipError_t leave(hipStream_t st, int P, hipEvent_t* ev) {
         const hipError_t he = hipEventRecord(done[next], st);
-        *last = done[next];
-        next = (next + 1) % kTeamsInFlight;
+        *ev = done[next];
+        for (int i = 0, first = next; i < places(P); ++i) {
+            last[next] = first;
+            next = (next + 1) % PLACES;
+        }
         return he;
     }
 };
@@ -1468,8 +1485,11 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             F.team_ub = team.ub;
             F.team_blk = team.blk_ints;
             F.team_rows = team.rows;
-            // reloads of one wait: over a second at the 0.5 us of a reload; EDB_SPIN_US bounds it for tests
-            F.team_limit = std::getenv("EDB_SPIN_US") ? 2 * spin_us : 1 << 22;
+            // Members wait 10 ms for the last one of their team (EDB_SPIN_US sets it for
+            // tests): longer than other work usually keeps them apart, and than walking a
+            // team alone takes.  Reloads of one wait for a row: over a second at 0.5 us each.
+            F.team_attend = 100 * (std::getenv("EDB_SPIN_US") ? std::clamp(std::atoi(std::getenv("EDB_SPIN_US")), 0, 1000000) : 10000);
+            F.team_limit = 1 << 22;
             F.off_x = F.off_f0 = F.off_f1 = F.off_rag = F.off_rptr = F.off_res = -1;
             align_hb(4);
             F.off_team = (int64_t)hb.size();
@@ -1481,7 +1501,7 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             hb.insert(hb.end(), team.fill_h.begin(), team.fill_h.end());
             hb.insert(hb.end(), team.fill_c.begin(), team.fill_c.end());
             F.off_ticket = n_counters;
-            n_counters += 2;
+            n_counters += 2 + team.C;
             e->team_batches.reserve(B - team.b0);
             for (int32_t b = team.b0; b < B; ++b) e->team_batches.push_back(lists(b));
             e->launches.push_back(F);
@@ -1805,6 +1825,7 @@ void build_calls(const edb_exec* e, const void* const* w, const void* x, void* a
             t.n_xrows = e->x_direct_rows;
             t.blk_ints = L.team_blk;
             t.limit = L.team_limit;
+            t.attend = L.team_attend;
             t.x = x;
             t.arena_h = arena_h;
             t.arena_c = reinterpret_cast<float*>(arena_c);
@@ -1871,7 +1892,7 @@ hipError_t launch_all(edb_exec* e, const void* const* w, const void* x, void* ar
         std::unique_lock<std::mutex> lk;
         if (c.form == 5 && gate) {
             lk = std::unique_lock<std::mutex>(gate->mu);
-            he = gate->enter(st);
+            he = gate->enter(st, c.t.P);
             if (he != hipSuccess) return he;
         }
         if (prof)
@@ -1879,7 +1900,7 @@ hipError_t launch_all(edb_exec* e, const void* const* w, const void* x, void* ar
                                     e->events[2 * c.launch + 1], 0);
         else
             he = hipLaunchKernel(c.fn, dim3(c.grid), dim3(c.block), c.args(), c.lds, st);
-        if (he == hipSuccess && lk.owns_lock()) he = gate->leave(st, &e->team_done);
+        if (he == hipSuccess && lk.owns_lock()) he = gate->leave(st, c.t.P, &e->team_done);
         if (he != hipSuccess) return he;
     }
     return hipGetLastError();
@@ -1909,7 +1930,7 @@ struct Topo {
     uint64_t owner = 0;            // executor (id) and pointers the nodes or calls hold now
     std::vector<const void*> owner_ptrs;
     std::vector<Call> calls;       // a short sequence: its calls, issued one by one (no graph)
-    bool team = false;             // its last call is a team launch
+    int team = 0;                  // its last call is a team launch with teams of so many work-groups
 };
 struct TopoSet {
     std::mutex mu;
@@ -1987,7 +2008,6 @@ hipError_t graph_launch(edb_exec* e, const void* const* w, const void* x, void* 
             }
             Topo n;
             n.sig = sig;
-            n.team = !calls.empty() && calls.back().form == 5;   // a team launch is the last of its sequence
             if (!list) {
                 he = hipGraphCreate(&n.graph, 0);
                 n.nodes.resize(calls.size());
@@ -2008,6 +2028,7 @@ hipError_t graph_launch(edb_exec* e, const void* const* w, const void* x, void* 
             t = &ts->t.back();
         }
         if (list) t->calls = calls;
+        t->team = !calls.empty() && calls.back().form == 5 ? calls.back().t.P : 0;   // a team launch is the last of its sequence
         t->owner = e->id;
         t->owner_ptrs = ptrs;
     }
@@ -2016,7 +2037,7 @@ hipError_t graph_launch(edb_exec* e, const void* const* w, const void* x, void* 
     auto enter = [&]() -> hipError_t {
         if (!t->team) return hipSuccess;
         glk = std::unique_lock<std::mutex>(gate->mu);
-        return gate->enter(st);
+        return gate->enter(st, t->team);
     };
     if (t->exec) {
         he = enter();
@@ -2026,7 +2047,7 @@ hipError_t graph_launch(edb_exec* e, const void* const* w, const void* x, void* 
         if (he == hipSuccess && c.form == 5) he = enter();
         if (he == hipSuccess) he = hipLaunchKernel(c.fn, dim3(c.grid), dim3(c.block), c.args(), c.lds, st);
     }
-    if (he == hipSuccess && glk.owns_lock()) he = gate->leave(st, &e->team_done);
+    if (he == hipSuccess && glk.owns_lock()) he = gate->leave(st, t->team, &e->team_done);
     if (he == hipSuccess && t->done) he = hipEventRecord(t->done, st);
     return he;
 }
@@ -2769,9 +2790,9 @@ bool v_team(VCheck& c, const edb_exec* e, const Launch& L, const std::string& wh
         return c.fail(what + ": grid");
     if (L.team_P * 16 * L.team_ub < e->H || (L.team_P - 1) * 16 * L.team_ub >= e->H) return c.fail(what + ": units");
     if (L.off_team < 0 || L.off_team % 4 || L.off_team + 2LL * L.team_C > ni) return c.fail(what + ": table of the teams");
-    if (L.off_ticket < e->off_counters || L.off_ticket + 2 > e->off_counters + e->n_counters)
+    if (L.off_ticket < e->off_counters || L.off_ticket + 2 + L.team_C > e->off_counters + e->n_counters)
         return c.fail(what + ": ticket outside the counter region");
-    if (L.team_limit < 1) return c.fail(what + ": wait bound");
+    if (L.team_limit < 1 || L.team_attend < 0) return c.fail(what + ": wait bound");
     std::vector<int64_t> mine((size_t)n_slots, -1);   // team that writes the row in this launch
     int64_t total = 0;
     for (int tm = 0; tm < L.team_C; ++tm) {

@@ -21,12 +21,18 @@
 //
 // Progress.  A work-group takes its place from a ticket counter when it
 // starts, so the members of a team are the next P work-groups that run,
-// wherever the hardware placed them: of the work-groups resident at any time
-// at most P - 1 per launch belong to a team whose other members are not
-// running yet, and all others finish and make room.  The host keeps few team
-// launches in flight at once, so that such incomplete teams cannot fill the
-// device between them.  Each wait is bounded all the same: past `limit` reloads a wave sets the error word, stops
-// waiting for the rest of the launch and goes on, so the launch always ends.
+// wherever the hardware placed them, and only the last team started can be
+// incomplete.  Its members may hold the CUs its missing ones wait for, between
+// them and those of other launches (of other processes too), so they wait for
+// the last one a bounded time only: the last member to start sets the team's
+// state to full; one whose time is up before sets it to left, and then all but
+// the last end without having written anything, which makes room.  The last,
+// whenever it starts, finds it so and walks the team's rows alone, unit block
+// by unit block (as many times slower, the same results).  A full team's
+// members all run, so its waits for rows end; each is bounded all the same:
+// past `limit` reloads a wave sets the error word, stops waiting for the rest
+// of the launch and goes on.  The host keeps few team launches in flight at
+// once, so that the slow way is not met within a process.
 //
 // Work of a tile: 8 waves split the reduction (k-group kg to wave kg % 8),
 // the partial sums meet in LDS, and the threads that take a (row, unit) add
@@ -48,6 +54,7 @@ constexpr int TEAM_CH = 32;                 // children of a child-sum tile
 constexpr int TEAM_WORDS = 16;              // words of a lattice-character tile
 constexpr int TEAM_TILE_INTS = 8;           // {type, rows, first row, first child, children, most children, 4-row form, tiles of the batch from here}
 constexpr int TEAM_REC_INTS = 8;            // {result slot, x row, child slots, their local rows, ragged range}
+constexpr int TEAM_FULL = 1, TEAM_LEFT = 2;    // states of a team
 constexpr uint32_t TEAM_EMPTY = 0xFFFFFFFFu;   // a word of a row that is not written yet
 
 struct TeamType {
@@ -62,7 +69,8 @@ struct TeamArgs {
     TeamType t[2];
     const int* ibuf;     // descriptor ints
     int off_table;       // per team {offset of its block in ibuf, ints of the block}
-    int* ticket;         // {ticket, error}, zero before the launch
+    int* ticket;         // {ticket, error, state of each team}, zero before the launch
+    int attend;          // how long members wait for the last one, in ticks of 10 ns
     int P, C, H, n_slots, n_xrows;
     int blk_ints;        // LDS room for a team's block
     int limit;           // reloads of one wait before it gives up
@@ -661,6 +669,87 @@ struct Team {
     }
 };
 
+// The team's state as the member at place p leaves its start: full, or left.
+// `seen`: what the last member found in its place.
+__device__ __forceinline__ int team_attend(int* state, int seen, bool last, int ticks) {
+    auto swap = [&](int to) {
+        int was = 0;
+        __hip_atomic_compare_exchange_strong(state, &was, to, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return was;
+    };
+    if (last) return seen ? seen : TEAM_FULL;
+    const uint64_t end = wall_clock64() + (uint64_t)ticks;
+    for (;;) {
+        int now = __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (!now && wall_clock64() >= end) {
+            now = swap(TEAM_LEFT);
+            if (!now) now = TEAM_LEFT;
+        }
+        if (now) return now;
+        __builtin_amdgcn_s_sleep(1);
+    }
+}
+
+// What a work-group of a team does, in LDS whose block of descriptors is loaded:
+// the weights of its units in registers, and the walk over the tiles.
+template <typename T, int NK, int UB, int K0, int K1>
+struct Walker {
+    using TM = Team<T, NK, UB, K0, K1>;
+    static constexpr int G0 = Kind<K0>::G, G1 = K1 < 0 ? 1 : Kind<K1 < 0 ? 0 : K1>::G;
+    TM tm;
+    uint4 w0[UB][NK][G0], w1[UB][NK][G1], wr[UB][NK][1];
+
+    __device__ __forceinline__ Walker(const TeamArgs& a, float* lds, int tid)
+        : tm{a, lds, nullptr, nullptr, nullptr, lds + TM::L::BLK + a.blk_ints, tid, tid & 63,
+             __builtin_amdgcn_readfirstlane(tid >> 6), 0} {
+        tm.blk = reinterpret_cast<const int*>(lds + TM::L::BLK);
+    }
+    // unit block p: its weights to registers, its biases to the LDS
+    __device__ __forceinline__ void load(int p) {
+        const TeamArgs& a = tm.a;
+        tm.u0 = p * TM::TU;
+        tm.load_weights(w0, a.t[0].W, a.t[0].K / TM::KG, p);
+        if constexpr (K1 >= 0) tm.load_weights(w1, a.t[1].W, a.t[1].K / TM::KG, p);
+        if constexpr (Kind<K0>::RAG) tm.load_weights(wr, a.t[0].Wr, a.t[0].Hk / TM::KG, p);
+        if (a.t[0].W) tm.template load_bias<K0>(a.t[0], 0);
+        if constexpr (K1 >= 0)
+            if (a.t[1].W) tm.template load_bias<K1>(a.t[1], 1);
+    }
+    // the block of descriptors has arrived; returns its number of tiles
+    __device__ __forceinline__ int ready() {
+        const int nt = __builtin_amdgcn_readfirstlane(tm.blk[0]);
+        tm.rows = tm.blk + 4 + TEAM_TILE_INTS * nt;
+        tm.kids0 = tm.rows + TEAM_REC_INTS * __builtin_amdgcn_readfirstlane(tm.blk[1]);
+        return nt;
+    }
+    __device__ __forceinline__ void walk(int t, int t1) {
+        while (t < t1) {
+            const int* hdr = tm.blk + 4 + TEAM_TILE_INTS * t;
+            const int ty = __builtin_amdgcn_readfirstlane(hdr[0]), cnt = __builtin_amdgcn_readfirstlane(hdr[7]);
+            const bool four = sizeof(T) == 4 && K0 != K_CS_INT && __builtin_amdgcn_readfirstlane(hdr[6]) != 0;
+            const int t0 = t;
+            t += cnt;
+            if (K1 < 0 || ty == 0) {
+                if constexpr (sizeof(T) == 4 && K0 != K_CS_INT) {
+                    if (four) {
+                        tm.template step<K0, 4>(0, w0, wr, t0, cnt);
+                        continue;
+                    }
+                }
+                tm.template step<K0, 16>(0, w0, wr, t0, cnt);
+            } else if constexpr (K1 >= 0) {
+                if constexpr (sizeof(T) == 4) {
+                    if (four) {
+                        tm.template step<K1, 4>(1, w1, wr, t0, cnt);
+                        continue;
+                    }
+                }
+                tm.template step<K1, 16>(1, w1, wr, t0, cnt);
+            }
+        }
+    }
+};
+
 template <typename T, int NK, int UB, int K0, int K1>
 __global__ __launch_bounds__(TEAM_NT, 2) void team_kernel(TeamArgs a) {
     extern __shared__ __align__(16) float tsmem[];
@@ -672,48 +761,60 @@ __global__ __launch_bounds__(TEAM_NT, 2) void team_kernel(TeamArgs a) {
     const int id = __builtin_amdgcn_readfirstlane(place[0]);
     const int team = id / a.P, p = id - team * a.P;
     if (team >= a.C) return;
+    const bool last = p == a.P - 1;
+    int* state = a.ticket + 2 + team;
+    int seen = 0;
+    if (threadIdx.x == 0 && last)
+        __hip_atomic_compare_exchange_strong(state, &seen, TEAM_FULL, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     int* blk = reinterpret_cast<int*>(tsmem + L::BLK);
-    TM tm{a, tsmem, blk, blk, blk, tsmem + L::BLK + a.blk_ints, (int)threadIdx.x, (int)threadIdx.x & 63,
-          __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), p * TM::TU};
-    constexpr int G0 = Kind<K0>::G, G1 = K1 < 0 ? 1 : Kind<K1 < 0 ? 0 : K1>::G;
-    constexpr bool R0 = Kind<K0>::RAG;
-    uint4 w0[UB][NK][G0], w1[UB][NK][G1], wr[UB][NK][1];
-    tm.load_weights(w0, a.t[0].W, a.t[0].K / TM::KG, p);
-    if constexpr (K1 >= 0) tm.load_weights(w1, a.t[1].W, a.t[1].K / TM::KG, p);
-    if constexpr (R0) tm.load_weights(wr, a.t[0].Wr, a.t[0].Hk / TM::KG, p);
-    if (a.t[0].W) tm.template load_bias<K0>(a.t[0], 0);
-    if constexpr (K1 >= 0)
-        if (a.t[1].W) tm.template load_bias<K1>(a.t[1], 1);
+    Walker<T, NK, UB, K0, K1> w(a, tsmem, (int)threadIdx.x);
+    w.load(p);
     const int boff = a.ibuf[a.off_table + 2 * team], bn = a.ibuf[a.off_table + 2 * team + 1];
     for (int i = threadIdx.x; i < bn / 4; i += TEAM_NT)
         reinterpret_cast<int4*>(blk)[i] = reinterpret_cast<const int4*>(a.ibuf + boff)[i];
+    if (threadIdx.x == 0) place[1] = team_attend(state, seen, last, a.attend);
     __syncthreads();
-    const int nt = __builtin_amdgcn_readfirstlane(blk[0]);
-    tm.rows = blk + 4 + TEAM_TILE_INTS * nt;
-    tm.kids0 = tm.rows + TEAM_REC_INTS * __builtin_amdgcn_readfirstlane(blk[1]);
+    if (__builtin_amdgcn_readfirstlane(place[1]) != TEAM_LEFT) {
+        const int nt = w.ready();
+        w.walk(0, nt);
+        return;
+    }
+    if (!last) return;
+    // The last member of a team that the others left: every step (the tiles of a batch)
+    // with each unit block in turn.  No row is waited for, and the cell states are read
+    // back from the arena.  All of it is made anew for each block from values the
+    // compiler cannot see through: in one loop with the members' walk, or with
+    // anything kept from block to block, it takes registers there (lattices of 200
+    // units 176 us and 190) or scratch memory (0.5 us a forward even where unused).
+    const int nt = w.ready();
+    {
+        int* rows = const_cast<int*>(w.tm.rows);
+        int* kids = const_cast<int*>(w.tm.kids0);
+        for (int i = threadIdx.x; i < blk[1]; i += TEAM_NT) rows[TEAM_REC_INTS * i + 4] = rows[TEAM_REC_INTS * i + 5] = -1;
+        for (int i = threadIdx.x; i < blk[2]; i += TEAM_NT) kids[2 * i + 1] = -1;
+    }
     for (int t = 0; t < nt;) {
-        const int* hdr = blk + 4 + TEAM_TILE_INTS * t;
-        const int ty = __builtin_amdgcn_readfirstlane(hdr[0]), cnt = __builtin_amdgcn_readfirstlane(hdr[7]);
-        const bool four = sizeof(T) == 4 && K0 != K_CS_INT && __builtin_amdgcn_readfirstlane(hdr[6]) != 0;
-        const int t0 = t;
-        t += cnt;
-        if (K1 < 0 || ty == 0) {
-            if constexpr (sizeof(T) == 4 && K0 != K_CS_INT) {
-                if (four) {
-                    tm.template step<K0, 4>(0, w0, wr, t0, cnt);
-                    continue;
-                }
-            }
-            tm.template step<K0, 16>(0, w0, wr, t0, cnt);
-        } else if constexpr (K1 >= 0) {
-            if constexpr (sizeof(T) == 4) {
-                if (four) {
-                    tm.template step<K1, 4>(1, w1, wr, t0, cnt);
-                    continue;
-                }
-            }
-            tm.template step<K1, 16>(1, w1, wr, t0, cnt);
+        const int cnt = __builtin_amdgcn_readfirstlane(blk[4 + TEAM_TILE_INTS * t + 7]);
+        for (int q = p; q >= 0; --q) {
+            __threadfence();    // the blocks before have stored their rows and are done with the LDS
+            __syncthreads();
+            using Args = const __constant__ TeamArgs;
+            Args* ka = (Args*)__builtin_amdgcn_kernarg_segment_ptr();
+            int tid = threadIdx.x;
+            asm volatile("" : "+s"(ka));
+            asm volatile("" : "+v"(tid));
+            auto type = [&](int i) {
+                return TeamType{ka->t[i].W, ka->t[i].bias, ka->t[i].Wr, ka->t[i].br, ka->t[i].E, ka->t[i].Ep, ka->t[i].Hk, ka->t[i].Hu, ka->t[i].K};
+            };
+            const TeamArgs b{{type(0), type(1)}, ka->ibuf, ka->off_table, ka->ticket, ka->attend, ka->P, ka->C, ka->H, ka->n_slots,
+                             ka->n_xrows, ka->blk_ints, ka->limit, ka->x, ka->arena_h, ka->arena_c};
+            Walker<T, NK, UB, K0, K1> one(b, tsmem, tid);
+            one.ready();
+            one.load(q);
+            __syncthreads();
+            one.walk(t, t + cnt);
         }
+        t += cnt;
     }
 }
 

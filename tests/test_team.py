@@ -2,7 +2,7 @@
 their units' weights in registers and exchange h rows through the arena.
 CPU: the planned descriptors validate.  GPU: parity with the oracle at the
 edges of the kernels (widths, row remainders, absent and many children), NaN
-states, and the bounded wait."""
+states, teams walked alone and several in flight."""
 import functools
 
 import numpy as np
@@ -275,24 +275,105 @@ def test_team_nan_states(dtype):
         np.testing.assert_allclose(a[ok], b[ok], rtol=2e-2 if dtype == "bf16" else 1e-4, atol=1e-2 if dtype == "bf16" else 1e-6)
 
 
+def _dispatch(launches, seed, attend, late=0.0):
+    """Model of the device: launches of (P, C) in flight together, their
+    work-groups dealt to 8 XCDs of 32 CUs in turn, one to a CU, an XCD's queues
+    served in random order; `late` is the share of XCD 7's time lost to earlier
+    work.  A work-group takes the launch's next ticket; members of a full team
+    run for a while and end; one of an incomplete team holds its CU, with
+    `attend` for so many steps at most, then the team is left and its last
+    member runs alone.  Returns whether every launch ends, and how many teams
+    were left."""
+    rng = np.random.default_rng(seed)
+    queue = [[[x for x in range(P * C) if x % 8 == xcd] for xcd in range(8)] for P, C in launches]
+    ticket, cus = [0] * len(launches), [[] for _ in range(8)]      # (launch, team, end, started)
+    left, step = set(), 0
+    while any(any(q) for q in queue) or any(cus):
+        step += 1
+        if step > 4000:
+            return False, len(left)
+        for xcd in range(8):
+            room = 32 - len(cus[xcd])
+            if xcd == 7 and rng.random() < late:
+                room = 0
+            while room and any(q[xcd] for q in queue):
+                n = rng.choice([i for i, q in enumerate(queue) if q[xcd]])
+                queue[n][xcd].pop()
+                P, t = launches[n][0], ticket[n]
+                ticket[n] += 1
+                cus[xcd].append([n, t // P, None, step])
+                room -= 1
+        for xcd in range(8):
+            keep = []
+            for wg in cus[xcd]:
+                n, team, end, began = wg
+                P = launches[n][0]
+                full = ticket[n] >= (team + 1) * P
+                if end is None and (n, team) in left:
+                    if not full or began < max(w[3] for c in cus for w in c if w[:2] == [n, team]):
+                        continue                               # it has left
+                    wg[2] = step + 20                          # the last one, alone
+                elif end is None and full:
+                    wg[2] = step + 5
+                elif end is None and attend is not None and step - began > attend:
+                    left.add((n, team))
+                    continue
+                if wg[2] is None or wg[2] > step:
+                    keep.append(wg)
+            cus[xcd] = keep
+    return True, len(left)
+
+
+def test_team_launches_always_end():
+    """Launches that together may hold an XCD's 32 CUs with incomplete teams do
+    not stop: a left team's last member walks it alone.  (Members that waited for
+    each other without end did stop.)  What the host lets into flight at once, at
+    most 31 work-groups of incomplete teams, never comes to that."""
+    stopped = 0
+    for P, C, n in ((16, 16, 4), (13, 19, 4), (32, 8, 3)):
+        for seed in range(12):
+            late = (0.0, 0.9, 0.99)[seed % 3]
+            stopped += not _dispatch([(P, C)] * n, seed, None, late)[0]
+            ends, _ = _dispatch([(P, C)] * n, seed, 300, late)
+            assert ends, (P, C, n, seed)
+    assert stopped
+    for flight in ([(8, 32)] * 4, [(4, 64)] * 4, [(16, 16)] * 2, [(13, 19), (8, 32), (4, 64)], [(32, 8)]):
+        for seed in range(12):
+            ends, left = _dispatch(flight, seed, None, (0.0, 0.9, 0.99)[seed % 3])
+            assert ends and left == 0, (flight, seed)
+
+
 @pytest.mark.gpu
-def test_team_wait_bound(monkeypatch):
-    """With a bound of two reloads a wait that times out is reported, the
-    launch ends all the same, and the next executor is right."""
-    pytest.importorskip("torch")
-    w = _chains(100, 200, "f32", [12] * 6, 31)
-    monkeypatch.setenv("EDB_SPIN_US", "1")
-    f = edb.Forward(w, flags=0)
+@pytest.mark.parametrize("name", sorted(set(CASES) - NO_TEAM))
+def test_team_walked_alone(name, monkeypatch):
+    """With no time given to wait for a team's last member, most teams are left
+    and walked by that one alone: the same states bit for bit, eagerly, through
+    the kept sequence and through the one-call path, and no wait times out."""
+    torch = pytest.importorskip("torch")
+    w = CASES[name]()
+    f = edb.Forward(w)
     f.run()
-    try:
-        f.exec.check(f.stream.cuda_stream)
-    except L.EdbError as ex:
-        assert ex.status == L.EDB_ERR_HIP and "timed out" in str(ex)
-    monkeypatch.delenv("EDB_SPIN_US")
-    g = edb.Forward(w)
-    g.run()
-    h, c = g.states()
-    assert state_rel_err(h, c, *evaluate_workload(w)) <= 1e-4
+    h, c = f.states()
+    monkeypatch.setenv("EDB_SPIN_US", "0")
+    for flags in (0, L.USE_GRAPH):
+        g = edb.Forward(w, flags=flags)
+        assert _teams(g)
+        for _ in range(2):
+            g.arena_h.fill_(7.0)
+            g.arena_c.fill_(-7.0)
+            g.run()
+            h2, c2 = g.states()
+            np.testing.assert_array_equal(h2, h)
+            np.testing.assert_array_equal(c2, c)
+    fc = edb.ForwardCall(w.op_type, w.child_ptr, w.child_idx, w.x_row, w.n_types, edb.operand_shapes(w), f.cells,
+                         table=edb.LATTICE_TABLE if w.kinds == LAT else None)
+    f.arena_h.fill_(5.0)
+    fc.call([b.data_ptr() for b in f.weights], f.x.data_ptr(), f.arena_h.data_ptr(), f.arena_c.data_ptr(),
+            f.arena_h.shape[0], f.stream.cuda_stream)
+    h3, c3 = f.states()
+    np.testing.assert_array_equal(h3, h)
+    np.testing.assert_array_equal(c3, c)
+    torch.cuda.synchronize()
 
 
 @pytest.mark.gpu
