@@ -445,7 +445,11 @@ edb_status edb_graph_stats(int64_t* instantiated, int64_t* updated);
  * team launches among it) is walked by that one alone, with the same results;
  * the environment variable EDB_SPIN_US sets that time in microseconds for tests.
  * In a team whose work-groups all run every wait ends; each is bounded all the
- * same (over a second), and edb_exec_check reports one that ended at its bound.
+ * same (over a second; EDB_TEAM_RELOADS reloads of a row, for tests).  One that
+ * ended at its bound is reported by edb_exec_check, or by the next edb_execute,
+ * edb_forward or edb_forward_noalloc on the device, which runs nothing and
+ * returns EDB_ERR_HIP once (edb_forward_noalloc alone in a process, without any
+ * of the others before it, does not learn of it).
  *
  * Dataflow launches (a persistent kernel running a run of consecutive small
  * batches, each tile waiting only for the tiles that produce its operand

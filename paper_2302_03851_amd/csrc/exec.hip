@@ -630,6 +630,7 @@ struct TeamGate {
     hipEvent_t done[PLACES] = {};     // kept for the process
     int last[PLACES] = {-1, -1, -1, -1};   // event of the last launch at each place
     int next = 0;
+    int* error = nullptr;             // host memory: a wait of a team launch ended at its bound; kept for the process
 
     static int places(int P) { return P <= 8 ? 1 : P <= 16 ? 2 : PLACES; }
     // with mu held, before and after the launch on st of teams of P
@@ -700,8 +701,21 @@ hipError_t ctx_streams(DeviceCtx* ctx) {
     hipError_t he = hipSuccess;
     if (!ctx->upload) he = hipStreamCreateWithFlags(&ctx->upload, hipStreamNonBlocking);
     if (he == hipSuccess && !ctx->release) he = hipStreamCreateWithFlags(&ctx->release, hipStreamNonBlocking);
+    if (he == hipSuccess && !ctx->teams->error) {
+        void* word = nullptr;
+        he = hipHostMalloc(&word, 64, hipHostMallocCoherent);
+        if (he == hipSuccess) __atomic_store_n(&ctx->teams->error, new (word) int(0), __ATOMIC_RELEASE);
+    }
     return he;
 }
+
+// Whether a wait of a team launch ended at its bound since the last call that
+// asked (calls without an executor have no other way to tell); cleared by it.
+bool team_wait_ended(TeamGate* gate) {
+    int* const word = gate ? __atomic_load_n(&gate->error, __ATOMIC_ACQUIRE) : nullptr;
+    return word && __atomic_load_n(word, __ATOMIC_RELAXED) != 0 && __atomic_exchange_n(word, 0, __ATOMIC_RELAXED) != 0;
+}
+const char kTeamWaitEnded[] = ": a wait of an earlier team launch on this device ended at its bound; that launch's results are invalid";
 
 namespace {
 uint64_t next_exec_id() {
@@ -1487,9 +1501,10 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             F.team_rows = team.rows;
             // Members wait 10 ms for the last one of their team (EDB_SPIN_US sets it for
             // tests): longer than other work usually keeps them apart, and than walking a
-            // team alone takes.  Reloads of one wait for a row: over a second at 0.5 us each.
+            // team alone takes.  Reloads of one wait for a row: over a second at 0.5 us each
+            // (EDB_TEAM_RELOADS, for tests).
             F.team_attend = 100 * (std::getenv("EDB_SPIN_US") ? std::clamp(std::atoi(std::getenv("EDB_SPIN_US")), 0, 1000000) : 10000);
-            F.team_limit = 1 << 22;
+            F.team_limit = std::getenv("EDB_TEAM_RELOADS") ? std::clamp(std::atoi(std::getenv("EDB_TEAM_RELOADS")), 0, 1 << 22) : 1 << 22;
             F.off_x = F.off_f0 = F.off_f1 = F.off_rag = F.off_rptr = F.off_res = -1;
             align_hb(4);
             F.off_team = (int64_t)hb.size();
@@ -1826,6 +1841,7 @@ void build_calls(const edb_exec* e, const void* const* w, const void* x, void* a
             t.blk_ints = L.team_blk;
             t.limit = L.team_limit;
             t.attend = L.team_attend;
+            t.error = e->teams ? __atomic_load_n(&e->teams->error, __ATOMIC_ACQUIRE) : nullptr;
             t.x = x;
             t.arena_h = arena_h;
             t.arena_c = reinterpret_cast<float*>(arena_c);
@@ -2080,6 +2096,7 @@ extern "C" edb_status edb_execute(edb_exec_t* e, const void* const* w, const voi
     if (!e) return fail(EDB_ERR_INVALID, "edb_execute: exec is NULL");
     if (e->flags & EDB_DRYRUN) return EDB_OK;
     if (edb_status cs = check_exec_args(e, w, x, arena_h, arena_c, "edb_execute")) return cs;
+    if (team_wait_ended(e->teams.get())) return fail(EDB_ERR_HIP, std::string("edb_execute") + kTeamWaitEnded);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
     hipError_t he = hipSuccess;
     if (!e->uploaded) {   // descriptors are on the device
@@ -2307,8 +2324,10 @@ extern "C" edb_status edb_exec_check(edb_exec_t* e, void* stream) {
     for (const Launch& F : e->launches) {
         if (F.flow && c[F.f_error - e->off_counters] != 0)
             return fail(EDB_ERR_HIP, "edb_exec_check: a dataflow wait timed out; results are invalid");
-        if (F.team && c[F.off_ticket + 1 - e->off_counters] != 0)
+        if (F.team && c[F.off_ticket + 1 - e->off_counters] != 0) {
+            (void)team_wait_ended(e->teams.get());   // told now
             return fail(EDB_ERR_HIP, "edb_exec_check: a wait of the team launch timed out; results are invalid");
+        }
     }
     return EDB_OK;
 }
@@ -2412,6 +2431,7 @@ edb_status edb::forward_on_stream(const edb_graph_t* g, const edb_schedule_t* s,
     if (he == hipSuccess) he = device_ctx(dev, &ctx);
     if (he == hipSuccess) he = ctx_streams(ctx);
     if (he != hipSuccess) return fail(EDB_ERR_HIP, std::string("edb_forward: ") + hipGetErrorString(he));
+    if (team_wait_ended(ctx->teams.get())) return fail(EDB_ERR_HIP, std::string("edb_forward") + kTeamWaitEnded);
     edb_exec_t* e = nullptr;
     edb_status st = prepare_impl(g, s, p, cells, flags, true, &e);
     if (st == EDB_OK) st = check_exec_args(e, packed_weights, x, arena_h, arena_c, "edb_forward");
@@ -2641,6 +2661,7 @@ extern "C" edb_status edb_forward_noalloc(int32_t n_nodes, int32_t n_types, cons
         }
     }
     if (he != hipSuccess) return fail(EDB_ERR_HIP, std::string("edb_forward_noalloc: ") + hipGetErrorString(he));
+    if (team_wait_ended(ctx->teams.get())) return fail(EDB_ERR_HIP, std::string("edb_forward_noalloc") + kTeamWaitEnded);
     edb_graph_t* g = nullptr;
     edb_schedule_t* s = nullptr;
     edb_plan_t* p = nullptr;
@@ -2792,7 +2813,7 @@ bool v_team(VCheck& c, const edb_exec* e, const Launch& L, const std::string& wh
     if (L.off_team < 0 || L.off_team % 4 || L.off_team + 2LL * L.team_C > ni) return c.fail(what + ": table of the teams");
     if (L.off_ticket < e->off_counters || L.off_ticket + 2 + L.team_C > e->off_counters + e->n_counters)
         return c.fail(what + ": ticket outside the counter region");
-    if (L.team_limit < 1 || L.team_attend < 0) return c.fail(what + ": wait bound");
+    if (L.team_limit < 0 || L.team_attend < 0) return c.fail(what + ": wait bound");
     std::vector<int64_t> mine((size_t)n_slots, -1);   // team that writes the row in this launch
     int64_t total = 0;
     for (int tm = 0; tm < L.team_C; ++tm) {

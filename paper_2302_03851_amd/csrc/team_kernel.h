@@ -30,7 +30,7 @@
 // whenever it starts, finds it so and walks the team's rows alone, unit block
 // by unit block (as many times slower, the same results).  A full team's
 // members all run, so its waits for rows end; each is bounded all the same:
-// past `limit` reloads a wave sets the error word, stops waiting for the rest
+// past `limit` reloads a wave sets the error words, stops waiting for the rest
 // of the launch and goes on.  The host keeps few team launches in flight at
 // once, so that the slow way is not met within a process.
 //
@@ -70,6 +70,7 @@ struct TeamArgs {
     const int* ibuf;     // descriptor ints
     int off_table;       // per team {offset of its block in ibuf, ints of the block}
     int* ticket;         // {ticket, error, state of each team}, zero before the launch
+    int* error;          // the host's error word (host memory), or none
     int attend;          // how long members wait for the last one, in ticks of 10 ns
     int P, C, H, n_slots, n_xrows;
     int blk_ints;        // LDS room for a team's block
@@ -213,8 +214,10 @@ struct Team {
     __device__ __forceinline__ void wait(LD ld, OK ok) {
         for (int tries = 0; !__all(ok()); ++tries) {
             if (dead || tries >= a.limit) {
-                if (!dead && lane == 0)
+                if (!dead && lane == 0) {
                     __hip_atomic_store(a.ticket + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (a.error) __hip_atomic_store(a.error, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+                }
                 dead = true;
                 break;
             }
@@ -806,7 +809,7 @@ __global__ __launch_bounds__(TEAM_NT, 2) void team_kernel(TeamArgs a) {
             auto type = [&](int i) {
                 return TeamType{ka->t[i].W, ka->t[i].bias, ka->t[i].Wr, ka->t[i].br, ka->t[i].E, ka->t[i].Ep, ka->t[i].Hk, ka->t[i].Hu, ka->t[i].K};
             };
-            const TeamArgs b{{type(0), type(1)}, ka->ibuf, ka->off_table, ka->ticket, ka->attend, ka->P, ka->C, ka->H, ka->n_slots,
+            const TeamArgs b{{type(0), type(1)}, ka->ibuf, ka->off_table, ka->ticket, ka->error, ka->attend, ka->P, ka->C, ka->H, ka->n_slots,
                              ka->n_xrows, ka->blk_ints, ka->limit, ka->x, ka->arena_h, ka->arena_c};
             Walker<T, NK, UB, K0, K1> one(b, tsmem, tid);
             one.ready();

@@ -377,6 +377,48 @@ def test_team_walked_alone(name, monkeypatch):
 
 
 @pytest.mark.gpu
+def test_team_wait_bound_is_reported(monkeypatch):
+    """Waits that give up at their first look (13 work-groups over 12 steps cannot
+    all find their rows written): the launch ends, edb_exec_check reports it, and
+    without it the next call of any kind does, once; what runs then is right."""
+    torch = pytest.importorskip("torch")
+    w = _chains(100, 200, "f32", [12] * 6, 31)
+    ok = edb.Forward(w)
+    ok.run()
+    h, c = ok.states()
+    monkeypatch.setenv("EDB_TEAM_RELOADS", "0")
+    f = edb.Forward(w, flags=0)
+    fc = edb.ForwardCall(w.op_type, w.child_ptr, w.child_idx, w.x_row, w.n_types, edb.operand_shapes(w), f.cells)
+    args = ([b.data_ptr() for b in f.weights], f.x.data_ptr(), f.arena_h.data_ptr(), f.arena_c.data_ptr(),
+            f.arena_h.shape[0], f.stream.cuda_stream)
+
+    def reported(call):
+        torch.cuda.synchronize()
+        with pytest.raises(L.EdbError) as ei:
+            call()
+        assert ei.value.status == L.EDB_ERR_HIP and ("timed out" in str(ei.value) or "its bound" in str(ei.value))
+
+    f.run()
+    reported(lambda: f.exec.check(f.stream.cuda_stream))
+    f.run()                                   # told already
+    reported(lambda: fc.call(*args))          # the next call of another kind
+    fc.call(*args)
+    reported(lambda: fc.call_noalloc(*args))
+    fc.call_noalloc(*args)
+    reported(ok.run)
+    monkeypatch.delenv("EDB_TEAM_RELOADS")
+    ok.arena_h.fill_(9.0)
+    ok.run()
+    h2, c2 = ok.states()
+    np.testing.assert_array_equal(h2, h)
+    np.testing.assert_array_equal(c2, c)
+    fc.call_noalloc(*args)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(f.arena_h.cpu().numpy()[f.plan.slot], h)
+    np.testing.assert_array_equal(f.arena_c.cpu().numpy()[f.plan.slot], c)
+
+
+@pytest.mark.gpu
 def test_team_launches_on_many_streams():
     """Sixteen threads with a stream each run team launches of different
     workloads at once, executors and one-call paths in turn: no wait times
