@@ -417,7 +417,8 @@ edb_status edb_prepare(const edb_graph_t* g, const edb_schedule_t* s, const edb_
  * later).  Up to 4 sequences per stream are kept, the least recently
  * used one replaced (after its last launch has run); they live until
  * edb_stream_release on the stream or the end of the process.  Kernel faults surface at the caller's next synchronisation.
- * One edb_exec_t must not run on two streams at once. */
+ * One edb_exec_t must not run on two streams at once.  A stream that is being
+ * captured is refused (EDB_ERR_HIP; the capture goes on). */
 edb_status edb_execute(edb_exec_t* e, const void* const* packed_weights, const void* x,
                        void* arena_h, void* arena_c, void* stream);
 
@@ -556,7 +557,9 @@ edb_status edb_stream_release(void* stream);
  * call reads before returning) and every kernel runs eagerly on `stream`.
  * Arguments and results are those of edb_forward (no executor is handed
  * back); EDB_USE_GRAPH, EDB_PROFILE and EDB_DRYRUN are rejected
- * (EDB_ERR_INVALID).  A mini-batch whose device memory exceeds the array is
+ * (EDB_ERR_INVALID).  A mini-batch whose device memory exceeds the array runs
+ * without the split tile and the team launch if that makes it fit (the same
+ * results within fp32 rounding), and is else
  * rejected with EDB_ERR_UNSUPPORTED before anything is enqueued.  The call
  * makes no hipMalloc, hipFree, stream or event creation.  Every call on a
  * device shares that device's array and the array keeps the last call's

@@ -627,7 +627,7 @@ int best_large(int kk, int dtype, int G, int m, int K, int Hu, int n_cu, int max
 struct TeamGate {
     static constexpr int PLACES = 4;
     std::mutex mu;
-    hipEvent_t done[PLACES] = {};     // kept for the process
+    hipEvent_t done[PLACES] = {};     // made with the device's streams, kept for the process
     int last[PLACES] = {-1, -1, -1, -1};   // event of the last launch at each place
     int next = 0;
     int* error = nullptr;             // host memory: a wait of a team launch ended at its bound; kept for the process
@@ -635,8 +635,6 @@ struct TeamGate {
     static int places(int P) { return P <= 8 ? 1 : P <= 16 ? 2 : PLACES; }
     // with mu held, before and after the launch on st of teams of P
     hipError_t enter(hipStream_t st, int P) {
-        if (!done[next])
-            if (hipError_t he = hipEventCreateWithFlags(&done[next], hipEventDisableTiming)) return he;
         for (int i = 0, waited = -1; i < places(P); ++i) {
             const int ev = last[(next + i) % PLACES];
             if (ev < 0 || ev == waited) continue;
@@ -701,12 +699,23 @@ hipError_t ctx_streams(DeviceCtx* ctx) {
     hipError_t he = hipSuccess;
     if (!ctx->upload) he = hipStreamCreateWithFlags(&ctx->upload, hipStreamNonBlocking);
     if (he == hipSuccess && !ctx->release) he = hipStreamCreateWithFlags(&ctx->release, hipStreamNonBlocking);
+    for (hipEvent_t& ev : ctx->teams->done)
+        if (he == hipSuccess && !ev) he = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
     if (he == hipSuccess && !ctx->teams->error) {
         void* word = nullptr;
         he = hipHostMalloc(&word, 64, hipHostMallocCoherent);
         if (he == hipSuccess) __atomic_store_n(&ctx->teams->error, new (word) int(0), __ATOMIC_RELEASE);
     }
     return he;
+}
+
+// Whether st is being captured into a graph (or the runtime cannot say now: the
+// legacy stream while another is captured).
+bool is_capturing(hipStream_t st) {
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cs) == hipSuccess) return cs != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
 }
 
 // Whether a wait of a team launch ended at its bound since the last call that
@@ -1897,7 +1906,7 @@ void build_calls(const edb_exec* e, const void* const* w, const void* x, void* a
     }
 }
 
-// gate: the device's team launches (NULL: the caller orders its calls on the device).
+// gate: the device's team launches (NULL: a captured launch, whose replays it cannot order).
 hipError_t launch_all(edb_exec* e, const void* const* w, const void* x, void* arena_h, void* arena_c,
                       hipStream_t st, TeamGate* gate) {
     thread_local std::vector<Call> calls;
@@ -2051,7 +2060,7 @@ hipError_t graph_launch(edb_exec* e, const void* const* w, const void* x, void* 
     t->used = ++ts->tick;
     std::unique_lock<std::mutex> glk;
     auto enter = [&]() -> hipError_t {
-        if (!t->team) return hipSuccess;
+        if (!t->team || !gate) return hipSuccess;
         glk = std::unique_lock<std::mutex>(gate->mu);
         return gate->enter(st, t->team);
     };
@@ -2098,6 +2107,8 @@ extern "C" edb_status edb_execute(edb_exec_t* e, const void* const* w, const voi
     if (edb_status cs = check_exec_args(e, w, x, arena_h, arena_c, "edb_execute")) return cs;
     if (team_wait_ended(e->teams.get())) return fail(EDB_ERR_HIP, std::string("edb_execute") + kTeamWaitEnded);
     hipStream_t st = reinterpret_cast<hipStream_t>(stream);
+    // the executor's and the team gate's events belong to executions, not to a graph's replays
+    if (is_capturing(st)) return fail(EDB_ERR_HIP, "edb_execute: the stream is being captured (edb_forward_noalloc can be)");
     hipError_t he = hipSuccess;
     if (!e->uploaded) {   // descriptors are on the device
         he = hipEventQuery(e->ready);
@@ -2546,8 +2557,9 @@ edb_status edb::forward_on_stream(const edb_graph_t* g, const edb_schedule_t* s,
             e->dbuf = reinterpret_cast<int*>(sl.dev);
             e->dmem = nullptr;
             e->dmem_owned = false;
-            he = use_graph ? graph_launch(e, packed_weights, x, arena_h, arena_c, hs, e->teams.get())
-                           : launch_all(e, packed_weights, x, arena_h, arena_c, hs, e->teams.get());
+            TeamGate* const gate = is_capturing(hs) ? nullptr : e->teams.get();
+            he = use_graph ? graph_launch(e, packed_weights, x, arena_h, arena_c, hs, gate)
+                           : launch_all(e, packed_weights, x, arena_h, arena_c, hs, gate);
         }
         if (he == hipSuccess) he = hipEventRecord(sl.done, hs);
         if (he == hipSuccess) {
@@ -2697,7 +2709,13 @@ extern "C" edb_status edb_forward_noalloc(int32_t n_nodes, int32_t n_types, cons
         // (the host array is read before the call returns: a copy from pageable
         // memory is staged synchronously)
         he = hipMemcpyAsync(e->dbuf, e->hbuf.data(), e->hbuf.size() * sizeof(int32_t), hipMemcpyHostToDevice, hs);
-        if (he == hipSuccess) he = launch_all(e, packed_weights, x, arena_h, arena_c, hs, nullptr);
+        // (without the gate's events no other team launch has run, and this call makes none)
+        TeamGate* gate = is_capturing(hs) ? nullptr : e->teams.get();
+        if (gate) {
+            std::lock_guard<std::mutex> lk(g_ctx_mu);
+            if (!gate->done[TeamGate::PLACES - 1]) gate = nullptr;
+        }
+        if (he == hipSuccess) he = launch_all(e, packed_weights, x, arena_h, arena_c, hs, gate);
         if (he != hipSuccess) st = fail(EDB_ERR_HIP, std::string("edb_forward_noalloc: ") + hipGetErrorString(he));
     }
     const std::string err = st == EDB_OK ? std::string() : std::string(edb_last_error());

@@ -419,6 +419,43 @@ def test_team_wait_bound_is_reported(monkeypatch):
 
 
 @pytest.mark.gpu
+def test_captured_stream_is_refused():
+    """edb_execute on a stream under capture, its descriptors long uploaded: an
+    error, and neither the capture nor later team launches anywhere are harmed."""
+    torch = pytest.importorskip("torch")
+    w = _chains(16, 48, "bf16", [10, 9, 8, 8, 7], 45)
+    f, g = edb.Forward(w), edb.Forward(w, flags=0)
+    for e in (f, g):
+        assert _teams(e)
+        e.run()
+    h, c = f.states()
+    y = torch.zeros(64, device="cuda")
+    graph, st = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    args = ([b.data_ptr() for b in f.weights], f.x.data_ptr(), f.arena_h.data_ptr(), f.arena_c.data_ptr())
+    with torch.cuda.graph(graph, stream=st, capture_error_mode="thread_local"):
+        y += 1
+        for e in (f, g):
+            with pytest.raises(L.EdbError) as ei:
+                e.exec.execute(*args, st.cuda_stream)
+            assert ei.value.status == L.EDB_ERR_HIP and "captured" in str(ei.value)
+        y += 1
+    for n in range(1, 4):
+        graph.replay()
+        for e in (f, g):
+            e.arena_h.fill_(4.0)
+            e.run()
+            h2, c2 = e.states()
+            np.testing.assert_array_equal(h2, h)
+            np.testing.assert_array_equal(c2, c)
+        assert bool((y == 2 * n).all())
+    for _ in range(6):       # past every place of the gate
+        g.run()
+    h2, _ = g.states()
+    np.testing.assert_array_equal(h2, h)
+
+
+@pytest.mark.gpu
 def test_team_launches_on_many_streams():
     """Sixteen threads with a stream each run team launches of different
     workloads at once, executors and one-call paths in turn: no wait times
