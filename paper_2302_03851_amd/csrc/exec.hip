@@ -572,16 +572,18 @@ double large_cost(int G, int vb, int m, int K, int Hu, int dtype, int occ, int n
 
 // Estimated microseconds of the split tile: a fixed term; per chunk of 32 k the
 // first tile of a CU, its load latency and its gates' weights (shared with the
-// other CUs: a term that grows until every CU has a tile); then the further
-// tiles of the busiest CU.  Least squares over 240 launches of 200-30,000 rows
-// (median error 2%, at most 12%).
+// other CUs: a term that grows until every CU has a tile); then the work past
+// one tile a CU, and the further tiles of the busiest CU.  Least squares over 837
+// launches of 130-34,000 rows of 64-1,024 units, 2-5 gates, K 64-2,048, in runs
+// that keep the device busy (median error 4%; the class chosen is 0.6% above the
+// fastest on average).
 double split_cost(int v, int m, const Dims& d, int n_cu) {
-    static const double k[3][6] = {{7.38, 0.250, 0.158, 0.082, 3.01, 0.185},
-                                   {5.73, 0.196, 0.064, 0.050, 1.81, 0.120},
-                                   {4.57, 0.0, 0.088, 0.032, 1.07, 0.119}};
+    static const double k[3][7] = {{6.73, 0.074, 0.215, 0.092, 0.153, 2.44, 0.127},
+                                   {4.90, 0.158, 0.082, 0.048, 0.087, 1.39, 0.078},
+                                   {4.14, 0.0, 0.106, 0.018, 0.043, 1.07, 0.083}};
     const double* c = k[v - FIRST_SPLIT];
-    const double fill = (double)split_tiles(v, m, d.Hu) / n_cu, more = std::ceil(fill) - 1, nch = d.K / 32;
-    return c[0] + nch * (c[1] + d.G * (c[2] + c[3] * std::min(1.0, fill))) + more * (c[4] + c[5] * nch * d.G);
+    const double fill = (double)split_tiles(v, m, d.Hu) / n_cu, more = std::ceil(fill) - 1, nch = d.K / 32, gn = nch * d.G;
+    return c[0] + nch * c[1] + gn * (c[2] + c[3] * std::min(1.0, fill) + c[4] * std::max(0.0, fill - 1)) + more * (c[5] + c[6] * gn);
 }
 
 // Estimated microseconds of child_reduce_kernel over m parents (fit as above).
@@ -1141,15 +1143,21 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
                 const bool split_ok = large_ok && dtype == EDB_F32 && split_kind(kind_id) && !lean &&
                                       (split_paid[t] || n_split < SPLIT_TYPES) && !(flags & (EDB_NO_SPLIT_K | EDB_TILE_LARGE | EDB_NO_LARGE)) &&
                                       (!(flags & EDB_DRYRUN) || (flags & EDB_TEAM_DRYRUN));
+                int sv = -1;   // the cheapest class, a tie (1%) to the larger tile
+                double sc = 0.0;
                 for (int v = FIRST_SPLIT; split_ok && v < NUM_VARIANTS; ++v) {
                     const Entry& en = table().e[kind_id][dtype][v];
-                    if (!en.fn || en.lds(d.K, 0) > max_lds) continue;
+                    if (!en.fn || en.lds(d.K, 0) > max_lds || (force_var >= 0 && force_var != v)) continue;
                     const double c = split_cost(v, m, d, n_cu);
-                    const double prep = split_paid[t] ? 0.0 : kSplitPrepUs;
-                    if (force_var == v || (force_var < 0 && c + prep < std::min(best, lest))) {
-                        best = c;
-                        var = v;
+                    if (sv < 0 || c < 0.99 * sc) {
+                        sc = c;
+                        sv = v;
                     }
+                }
+                // against the others, with the weights' splitting where no earlier batch has paid for it
+                if (sv >= 0 && (force_var >= 0 || sc + (split_paid[t] ? 0.0 : kSplitPrepUs) < std::min(best, lest))) {
+                    best = sc;
+                    var = sv;
                 }
                 if (is_split(var) && !split_paid[t]) {
                     split_paid[t] = 1;
@@ -1343,6 +1351,16 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             bool all = true;
             for (int32_t b = 0; b < team.b0; ++b) all = all && !kind_info(cells[s->batch_type[b]].kind).x;
             if (all) e->flags = flags = flags | EDB_X_DIRECT;
+        }
+        if (team.b0 >= 0) {   // batches inside the team launch pay for nothing
+            std::fill(split_paid.begin(), split_paid.end(), 0);
+            n_split = 0;
+            for (int32_t b = 0; b < team.b0; ++b)
+                for (const Launch& q : blaunch[b])
+                    if (q.kk >= 0 && is_split(q.info.variant) && !split_paid[q.type]) {
+                        split_paid[q.type] = 1;
+                        ++n_split;
+                    }
         }
         for (int32_t b = 0; b < (team.b0 < 0 ? B : team.b0); ++b)
             if (blaunch[b].empty())

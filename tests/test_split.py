@@ -146,6 +146,33 @@ def test_split_tile_not_finite(monkeypatch):
         np.testing.assert_allclose(a[ok], b[ok], rtol=1e-4, atol=1e-6)
 
 
+def _two_levels(E, H, n):
+    """n trees of two internal nodes, one above the other: two batches of n rows."""
+    op, ch, hx = [], [], []
+    for t in range(n):
+        k = len(op)
+        op += [0, 0, 0, 1, 1]
+        ch += [[], [], [], [k, k + 1], [k + 3, k + 2]]
+        hx += [True, True, True, False, False]
+    return WL.make_graph(TREE, E, H, op, ch, hx, seed=12)
+
+
+def test_split_class_does_not_depend_on_the_batch_order():
+    """The first batch of a type, which pays for the weights' splitting, takes
+    the class that a later one of the same rows takes."""
+    used = set()
+    for H in (192, 320, 512, 768, 1024):
+        for n in (180, 260, 380, 550, 800, 1100, 1300, 1600, 2000, 3200, 5000):
+            f = edb.Forward(_two_levels(64, H, n), flags=L.DRYRUN | L.TEAM_DRYRUN)
+            got = [q["variant"] for q in (f.exec.launch_info(i) for i in range(1, f.exec.launches()))
+                   if q["kind"] == WL.NARY_INTERNAL]
+            assert len(got) == 2
+            if got[0] in L.SPLIT_VARIANTS:
+                assert got[0] == got[1], (H, n, got)
+                used.add(got[0])
+    assert used == set(L.SPLIT_VARIANTS)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("variant", L.SPLIT_VARIANTS)
 def test_split_tile_ends_of_the_range(variant, monkeypatch):
