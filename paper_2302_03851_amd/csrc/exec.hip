@@ -1385,9 +1385,13 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
                 b = b1;
             }
         }
-        // row of every node inside its batch (for dependency lists)
-        std::vector<int32_t> node_batch(g->V, -1), node_row(g->V, -1);
-        for (int32_t b = 0; b < B; ++b)
+        // row of every node inside its batch (for dataflow launches' dependency lists)
+        std::vector<int32_t> node_batch, node_row;
+        if (flow_on) {
+            node_batch.assign(g->V, -1);
+            node_row.assign(g->V, -1);
+        }
+        for (int32_t b = 0; b < (flow_on ? B : 0); ++b)
             for (int32_t i = s->batch_ptr[b]; i < s->batch_ptr[b + 1]; ++i) {
                 node_batch[p->order[i]] = b;
                 node_row[p->order[i]] = i - s->batch_ptr[b];
@@ -1544,8 +1548,10 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             hb.insert(hb.end(), team.fill_c.begin(), team.fill_c.end());
             F.off_ticket = n_counters;
             n_counters += 2 + team.C;
-            e->team_batches.reserve(B - team.b0);
-            for (int32_t b = team.b0; b < B; ++b) e->team_batches.push_back(lists(b));
+            if (!noalloc) {   // for edb_split_phase; a call without an executor cannot ask for it
+                e->team_batches.reserve(B - team.b0);
+                for (int32_t b = team.b0; b < B; ++b) e->team_batches.push_back(lists(b));
+            }
             e->launches.push_back(F);
         }
         // counter region: zeroed by the staging kernel before every forward
