@@ -340,7 +340,9 @@ edb_status edb_pack_weights(const edb_cell* cell, const float* const* logical,
 
 /* ---- execution ------------------------------------------------------------ */
 #define EDB_USE_GRAPH    1  /* keep the call sequence per stream: a HIP graph, or a list of few calls */
-#define EDB_DRYRUN       2  /* record the launch list only; no HIP call (CPU testing) */
+#define EDB_DRYRUN       2  /* record a launch list only; no HIP call (CPU testing): one launch per batch (two per
+                               MV_VEC batch, three per child-sum batch on the large tile), without the split
+                               tile and the team launch unless EDB_TEAM_DRYRUN is set too */
 #define EDB_FORCE_GATHER 4  /* treat every CONTIG operand as indexed (ablation) */
 #define EDB_X_DIRECT     8  /* read x rows in place by x_row instead of staging them */
 #define EDB_PROFILE     16  /* eager launches timed by start/stop HIP events in each dispatch (edb_exec_launch_times) */
@@ -348,8 +350,9 @@ edb_status edb_pack_weights(const edb_cell* cell, const float* const* logical,
 #define EDB_NO_SPLIT_K  64  /* small tiles without split-K only (each accumulator sums its k-groups in order) */
 #define EDB_TILE_LARGE 128  /* the large bf16 tile for every batch it supports, whatever the batch size */
 #define EDB_NO_LARGE   256  /* never the large tile (ablation) */
-#define EDB_TEAM_DRYRUN 1024 /* with EDB_DRYRUN only: build the team launch as for a device of 256
-                               compute units, so that edb_exec_validate can check its descriptors */
+#define EDB_TEAM_DRYRUN 1024 /* with EDB_DRYRUN only: record the launches that a device of 256 compute units
+                               runs, with split tiles, MV_VEC batches in one launch and the team launch
+                               (whose descriptors edb_exec_validate then checks) */
 #define EDB_FLOW_DRYRUN 512 /* with EDB_DRYRUN only: build the dataflow launches (switched off on the
                                GPU) so that edb_exec_validate can check their descriptors */
 
@@ -395,9 +398,10 @@ edb_status edb_prepare(const edb_graph_t* g, const edb_schedule_t* s, const edb_
 
 /* Run one forward pass, asynchronously on `stream` (hipStream_t): the batches
  * in the order Algorithm 1 produced them, each as one launch of its fused
- * gather / cell GEMM / gate epilogue / scatter kernel (Section 3.1); with
- * EDB_USE_GRAPH the whole sequence is one graph launch (Section 1: fewer
- * kernel launches is the first reason batching pays).
+ * gather / cell GEMM / gate epilogue / scatter kernel (Section 3.1), or the
+ * last ones together as a team launch (below); with EDB_USE_GRAPH the sequence
+ * is kept per stream (Section 1: fewer kernel launches is the first reason
+ * batching pays).
  *   packed_weights host array [n_types] of device pointers (edb_pack_weights output)
  *   x        device [n_x_rows x in_dim] of the cells' dtype, rows addressed by x_row
  *   arena_h  device [n_slots x H] of the cells' dtype; node v's h is row slot[v]
@@ -444,7 +448,8 @@ edb_status edb_graph_stats(int64_t* instantiated, int64_t* updated);
  * depend on how rows were dealt.  A team whose last work-group does not start
  * within 10 ms of another (the CUs are held by other work, another process's
  * team launches among it) is walked by that one alone, with the same results;
- * the environment variable EDB_SPIN_US sets that time in microseconds for tests.
+ * the environment variable EDB_SPIN_US sets that time in microseconds for tests
+ * (-1: every team is walked so).
  * In a team whose work-groups all run every wait ends; each is bounded all the
  * same (over a second; EDB_TEAM_RELOADS reloads of a row, for tests).  One that
  * ended at its bound is reported by edb_exec_check, or by the next edb_execute,

@@ -1530,11 +1530,10 @@ edb_status prepare_impl(const edb_graph_t* g, const edb_schedule_t* s, const edb
             F.team_ub = team.ub;
             F.team_blk = team.blk_ints;
             F.team_rows = team.rows;
-            // Members wait 10 ms for the last one of their team (EDB_SPIN_US sets it for
-            // tests): longer than other work usually keeps them apart, and than walking a
-            // team alone takes.  Reloads of one wait for a row: over a second at 0.5 us each
-            // (EDB_TEAM_RELOADS, for tests).
-            F.team_attend = 100 * (std::getenv("EDB_SPIN_US") ? std::clamp(std::atoi(std::getenv("EDB_SPIN_US")), 0, 1000000) : 10000);
+            // Members wait 10 ms for the last one of their team, about what walking it
+            // alone takes (EDB_SPIN_US sets it for tests; -1: every team is left).  Reloads
+            // of one wait for a row: over a second at 0.5 us each (EDB_TEAM_RELOADS, for tests).
+            F.team_attend = 100 * (std::getenv("EDB_SPIN_US") ? std::clamp(std::atoi(std::getenv("EDB_SPIN_US")), -1, 1000000) : 10000);
             F.team_limit = std::getenv("EDB_TEAM_RELOADS") ? std::clamp(std::atoi(std::getenv("EDB_TEAM_RELOADS")), 0, 1 << 22) : 1 << 22;
             F.off_x = F.off_f0 = F.off_f1 = F.off_rag = F.off_rptr = F.off_res = -1;
             align_hb(4);
@@ -2855,7 +2854,7 @@ bool v_team(VCheck& c, const edb_exec* e, const Launch& L, const std::string& wh
     if (L.off_team < 0 || L.off_team % 4 || L.off_team + 2LL * L.team_C > ni) return c.fail(what + ": table of the teams");
     if (L.off_ticket < e->off_counters || L.off_ticket + 2 + L.team_C > e->off_counters + e->n_counters)
         return c.fail(what + ": ticket outside the counter region");
-    if (L.team_limit < 0 || L.team_attend < 0) return c.fail(what + ": wait bound");
+    if (L.team_limit < 0) return c.fail(what + ": wait bound");
     std::vector<int64_t> mine((size_t)n_slots, -1);   // team that writes the row in this launch
     int64_t total = 0;
     for (int tm = 0; tm < L.team_C; ++tm) {

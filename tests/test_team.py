@@ -346,16 +346,17 @@ def test_team_launches_always_end():
 @pytest.mark.gpu
 @pytest.mark.parametrize("name", sorted(set(CASES) - NO_TEAM))
 def test_team_walked_alone(name, monkeypatch):
-    """With no time given to wait for a team's last member, most teams are left
-    and walked by that one alone: the same states bit for bit, eagerly, through
-    the kept sequence and through the one-call path, and no wait times out."""
+    """Every team left by its members and walked by the last one alone, and with
+    no time given to wait for it some or none: the same states bit for bit,
+    eagerly, through the kept sequence and through the one-call path, and no
+    wait times out."""
     torch = pytest.importorskip("torch")
     w = CASES[name]()
     f = edb.Forward(w)
     f.run()
     h, c = f.states()
-    monkeypatch.setenv("EDB_SPIN_US", "0")
-    for flags in (0, L.USE_GRAPH):
+    for flags, spin in ((0, "-1"), (L.USE_GRAPH, "-1"), (0, "0")):
+        monkeypatch.setenv("EDB_SPIN_US", spin)
         g = edb.Forward(w, flags=flags)
         assert _teams(g)
         for _ in range(2):
@@ -368,6 +369,7 @@ def test_team_walked_alone(name, monkeypatch):
     fc = edb.ForwardCall(w.op_type, w.child_ptr, w.child_idx, w.x_row, w.n_types, edb.operand_shapes(w), f.cells,
                          table=edb.LATTICE_TABLE if w.kinds == LAT else None)
     f.arena_h.fill_(5.0)
+    monkeypatch.setenv("EDB_SPIN_US", "-1")
     fc.call([b.data_ptr() for b in f.weights], f.x.data_ptr(), f.arena_h.data_ptr(), f.arena_c.data_ptr(),
             f.arena_h.shape[0], f.stream.cuda_stream)
     h3, c3 = f.states()
