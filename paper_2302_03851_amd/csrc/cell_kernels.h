@@ -153,12 +153,14 @@ __device__ __forceinline__ float tanh_f(float z) {
 }
 
 // sigma(a) * tanh(b) from two exponentials and one reciprocal:
-// sgn(b) (1 - q) / ((1 + p)(1 + q)) with p = e^-a and q = e^{-2|b|}.  q stays in
-// (0, 1], and an overflowing p gives the exact limit 0; near b = 0 the error
-// of 1 - q is absolute (about 1e-7), not relative.
+// sgn(b) (1 - q) / ((1 + p)(1 + q)) with p = e^-a and q = e^{-2|b|}.  q is kept in
+// (0, 1], so that an overflowing p gives the exact limit 0 (infinity times a q of
+// zero would be NaN; a smallest normal q changes no other result); near b = 0 the
+// error of 1 - q is absolute (about 1e-7), not relative.
 __device__ __forceinline__ float sig_tanh(float a, float b) {
     const float p = __expf(-a);
-    const float q = __expf(-2.0f * fabsf(b));
+    float q = __expf(-2.0f * fabsf(b));
+    q = q < 0x1p-126f ? 0x1p-126f : q;   // NaN stays
     const float den = fmaf(p, q, p + q) + 1.0f;
     return copysignf((1.0f - q) * __builtin_amdgcn_rcpf(den), b);
 }
