@@ -17,7 +17,7 @@
 // lane in a row: no bank conflicts).  Bound by the matrix instructions (10,247
 // rows of 512 by 1,280: 75 us, 1,075 TFLOP/s of bf16 products, the rate of a
 // large bf16 matrix product on this card), and for fewer rows than fill the CUs
-// by a work-group's own chain of loads, 22, 13 and 11 us for 64, 32 and 16 rows
+// by a work-group's own chain of loads, 27, 15 and 13 us for 64, 32 and 16 rows
 // of that size.  Against the fp32 products of the large and streamed tiles, us:
 // 10,247 rows 167 and 75, 4,075 rows 53 and 32, 2,019 rows 30 and 19, 790 rows
 // 16.5 and 13.6, 30,842 rows of 256 by 768 131 and 75.
